@@ -171,6 +171,26 @@ vd_status vd_evict_step(const vd_cache_desc *desc, const int32_t *n_valid,
                         void *workspace, size_t workspace_bytes, vd_stream stream);
 
 /*
+ * vd_append -- new rows of one sequence into every unit's next slots (Sec.
+ * 2.2, Eq. block_processing: the block is concatenated before the eviction).
+ *   desc        K and V both required
+ *   seq         the sequence, 0 <= seq < num_seqs
+ *   n_old       its cached tokens; the rows go to slots [n_old, n_old + rows)
+ *   rows        >= 1, n_old + rows <= capacity
+ *   k_rows,     device; row r of (layer l, KV head h) starts at element
+ *   v_rows      l*strides[0] + h*strides[1] + r*strides[2] of the cache's
+ *               dtype, head_dim contiguous elements, every row 16-byte aligned
+ *   k_strides,  HOST arrays of three element strides, >= 0
+ *   v_strides
+ *   pos         device int32 [U][capacity] or NULL: slot n_old + r of every
+ *               unit of the sequence receives pos0 + r
+ * The rows must not overlap the cache (VD_ERR_INVALID_ARG).
+ */
+vd_status vd_append(const vd_cache_desc *desc, int32_t seq, int32_t n_old, int32_t rows,
+                    const void *k_rows, const int64_t *k_strides, const void *v_rows,
+                    const int64_t *v_strides, int32_t *pos, int32_t pos0, vd_stream stream);
+
+/*
  * vd_geometry -- key and value geometry of every unit (Sec. 3.1, the spread
  * of the distances to the centroid; Sec. 4, bos-cosim).
  *   desc        K and V both required (desc->k non-NULL)

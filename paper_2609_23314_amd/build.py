@@ -44,10 +44,11 @@ def _build_one(out: str, defines, verbose: bool) -> str:
         steps = [
             [cc, f"--offload-arch={ARCH}", *COMMON, *defines, *DEVICE_FLAGS, "-c",
              os.path.join(CSRC, "vd_kernels.hip"), "-o", os.path.join(tmp, "vd_kernels.o")],
+        ] + [
             [cc, *COMMON, *defines, "-x", "c++", "-D__HIP_PLATFORM_AMD__",
              "-I", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
-             "-c", os.path.join(CSRC, "vd_api.cpp"),
-             "-o", os.path.join(tmp, "vd_api.o")],
+             "-c", os.path.join(CSRC, name + ".cpp"), "-o", os.path.join(tmp, name + ".o")]
+            for name in ("vd_api", "vd_append")
         ]
         for cmd in steps:
             if verbose:

@@ -11,43 +11,14 @@
 #include <cstring>
 
 #include "vd.h"
+#include "vd_check.h"
 #include "vd_debug.h"
 #include "vd_launch.h"
 
 namespace {
 
+using namespace vd::host;
 using vd::UnitParams;
-
-int64_t elem_bytes(int32_t dtype) { return dtype == VD_DTYPE_BF16 ? 2 : 4; }
-int64_t align16(int64_t x) { return (x + 15) & ~int64_t(15); }
-bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
-
-vd_status check_desc(const vd_cache_desc *d) {
-    if (!d || !d->v) return VD_ERR_INVALID_ARG;
-    if (d->dtype != VD_DTYPE_BF16 && d->dtype != VD_DTYPE_F32) return VD_ERR_INVALID_ARG;
-    if (d->num_seqs < 1 || d->num_layers < 1 || d->num_kv_heads < 1 || d->num_q_heads < 1)
-        return VD_ERR_INVALID_ARG;
-    if (d->num_q_heads % d->num_kv_heads != 0) return VD_ERR_INVALID_ARG;
-    if (d->head_dim < 1 || d->capacity < 1) return VD_ERR_INVALID_ARG;
-    if (d->head_dim != 64 && d->head_dim != 128 && d->head_dim != 256) return VD_ERR_UNSUPPORTED;
-    if (d->capacity > VD_MAX_CAPACITY) return VD_ERR_UNSUPPORTED;
-    if (d->stride_seq < 0 || d->stride_layer < 0 || d->stride_head < 0 || d->stride_slot < 0)
-        return VD_ERR_INVALID_ARG;
-    if (d->stride_slot < d->head_dim) return VD_ERR_INVALID_ARG;  // rows would overlap
-    if (d->num_layers > 65535) return VD_ERR_UNSUPPORTED;  // one grid row per layer
-    const int64_t units = int64_t(d->num_seqs) * d->num_layers * d->num_kv_heads;
-    if (units > INT32_MAX || units * int64_t(d->capacity) > (int64_t(1) << 47))
-        return VD_ERR_UNSUPPORTED;
-    const int64_t es = elem_bytes(d->dtype);
-    // a unit's slab is addressed with 32-bit byte offsets
-    if (int64_t(d->capacity) * d->stride_slot * es > int64_t(UINT32_MAX)) return VD_ERR_UNSUPPORTED;
-    const int64_t strides[4] = {d->stride_seq, d->stride_layer, d->stride_head, d->stride_slot};
-    for (int64_t s : strides)
-        if ((s * es) % 16 != 0) return VD_ERR_INVALID_ARG;  // every row 16-byte aligned
-    if (!aligned(d->v, 16) || (d->k && !aligned(d->k, 16))) return VD_ERR_INVALID_ARG;
-    if (d->k && d->k == d->v) return VD_ERR_INVALID_ARG;
-    return VD_OK;
-}
 
 vd_status check_counts(const vd_cache_desc *d, const int32_t *n_valid, const int32_t *budget) {
     if (!n_valid) return VD_ERR_INVALID_ARG;
@@ -129,8 +100,6 @@ vd_status plan_step_lds(const vd_cache_desc *d, UnitParams &p, int ns, bool scor
     lds_bytes = size_t(used + stash_rows * row_bytes);
     return VD_OK;
 }
-
-vd_status launched(hipError_t e) { return e == hipSuccess ? VD_OK : VD_ERR_HIP; }
 
 // Row splits of the fused decode attention: about 768 workgroups of 256
 // threads over the whole launch (three per CU, what stays resident at the

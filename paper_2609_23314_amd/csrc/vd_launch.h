@@ -87,6 +87,21 @@ hipError_t launch_compact(const UnitParams &p, int num_seqs, int dtype, int head
 constexpr int kAttnThreads = 256;
 hipError_t launch_attn(const UnitParams &p, int num_seqs, int dtype, int head_dim, int group,
                        bool caote, size_t split_lds, hipStream_t stream);
+// Appends rows to every unit of one sequence: K and V rows [units][rows] from
+// strided sources into slots [slot0, slot0 + rows), and their token indices.
+struct AppendParams {
+    char *k, *v;                        // the sequence's first unit in the cache
+    const char *src_k, *src_v;
+    int32_t *pos;                       // [units][capacity] of the sequence, or null
+    int64_t s_layer, s_head;            // cache strides in BYTES
+    int64_t k_layer, k_head, k_row;     // source strides in BYTES
+    int64_t v_layer, v_head, v_row;
+    uint32_t s_slot;
+    int32_t num_kv_heads, units, capacity, slot0, rows, pos0;
+    int32_t unit_shift;                 // log2 of the threads that take one unit (6 .. 8)
+    int32_t tiles;                      // workgroups per group of units
+};
+hipError_t launch_append(const AppendParams &p, int row_bytes, hipStream_t stream);
 hipError_t launch_geometry(const UnitParams &p, int num_seqs, int dtype, int head_dim,
                            size_t lds_bytes, hipStream_t stream);
 // Static device scratch of the allocation-free fused decode step (one copy per

@@ -26,7 +26,7 @@ MAX_CAPACITY = 16384
 
 EXPORTS = ("vd_score", "vd_select_topn", "vd_compact", "vd_evict_step",
            "vd_evict_step_workspace_size", "vd_status_string", "vd_stream_read",
-           "vd_geometry", "vd_decode_attention_evict", "vd_decode_attention_workspace_size",
+           "vd_append", "vd_geometry", "vd_decode_attention_evict", "vd_decode_attention_workspace_size",
            "vd_decode_attention_evict_noalloc", "vd_decode_attention_noalloc_max_bytes")
 
 
@@ -74,6 +74,8 @@ def load():
     lib.vd_status_string.restype = ctypes.c_char_p
     lib.vd_stream_read.argtypes = [P, SZ, P, P]
     lib.vd_stream_read.restype = ctypes.c_int
+    lib.vd_append.argtypes = [D, I32, I32, I32, P, P, P, P, P, I32, P]
+    lib.vd_append.restype = ctypes.c_int
     lib.vd_geometry.argtypes = [D, P, P, P, P, P]
     lib.vd_geometry.restype = ctypes.c_int
     lib.vd_decode_attention_evict.argtypes = [D, P, ctypes.c_float, P, P, I32, P, P, P, P, SZ, P]
@@ -219,6 +221,48 @@ def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=Non
         ctypes.byref(desc), _ptr(n_h), _ptr(b_h), VARIANTS[variant], _ptr(running_sum),
         _ptr(pos), _ptr(scores_out), _ptr(keep_out), _ptr(workspace), ws_bytes,
         _stream(v.device, stream)))
+
+
+def _append_rows_ok(x, like, L, H, D):
+    return (type(x) is torch.Tensor and x.dtype == like.dtype and x.device == like.device and x.dim() == 4
+            and x.shape[0] == L and x.shape[1] == H and x.shape[3] == D and x.stride(3) == 1
+            and not x.requires_grad and not x.is_neg())
+
+
+def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
+    """Rows [L, H, t, D] into slots [n_old, n_old + t) of sequence ``seq`` and
+    their indices pos0 + r into ``pos``, on the current stream.  True if the
+    library took the call; False, with nothing queued, for rows or caches that
+    are not what its kernel reads (another dtype, device or layout, rows that
+    overlap the cache), which a caller then copies with torch."""
+    if not (type(k) is torch.Tensor and type(v) is torch.Tensor and v.is_cuda and v.dim() == 5 and v.stride(4) == 1
+            and k.shape == v.shape and k.stride() == v.stride() and k.dtype == v.dtype and k.device == v.device
+            and v.dtype in (torch.bfloat16, torch.float32)):
+        return False
+    if k.requires_grad or v.requires_grad or k.is_neg() or v.is_neg():
+        return False
+    if (k.is_inference() or v.is_inference()) and not torch.is_inference_mode_enabled():
+        return False
+    S, L, H, C, D = v.shape
+    seq, n_old, pos0 = int(seq), int(n_old), int(pos0)
+    if not (_append_rows_ok(k_rows, k, L, H, D) and _append_rows_ok(v_rows, v, L, H, D)
+            and k_rows.shape[2] == v_rows.shape[2] and k_rows.shape[2] > 0 and 0 <= seq < S
+            and 0 <= n_old <= C and 0 <= pos0 < 2 ** 31):
+        return False
+    if pos is not None and not (type(pos) is torch.Tensor and pos.dtype == torch.int32 and pos.device == v.device
+                                and pos.shape == (S * L * H, C) and pos.is_contiguous()):
+        return False
+    if v.device.index != torch.cuda.current_device():
+        return False
+    strides = ctypes.c_int64 * 3
+    ks, vs = strides(*k_rows.stride()[:3]), strides(*v_rows.stride()[:3])
+    desc = cache_desc(v, k)
+    st = load().vd_append(ctypes.byref(desc), seq, n_old, k_rows.shape[2], k_rows.data_ptr(), ks,
+                          v_rows.data_ptr(), vs, _ptr(pos), pos0, _stream(v.device, None))
+    if st in (VD_ERR_INVALID_ARG, VD_ERR_UNSUPPORTED):
+        return False
+    _check("vd_append", st)
+    return True
 
 
 def vd_geometry(k, v, n_valid, out=None, *, k_sum=None, v_sum=None, stream=None):
