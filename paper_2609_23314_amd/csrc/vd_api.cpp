@@ -62,9 +62,12 @@ void hand_scored_rows(UnitParams &p, vd_variant variant) {
     if (key_side(variant)) std::swap(p.k, p.v);
 }
 
-// Plans the dynamic LDS of the pass kernel for one launch.
+// Plans the dynamic LDS of the pass kernel for one launch, with `threads` per
+// workgroup and at most `limit` bytes; with `stage_all` only if every row to
+// stage fits.
 vd_status plan_step_lds(const vd_cache_desc *d, UnitParams &p, int ns, bool score_mode,
-                        bool have_state, bool want_scores, size_t &lds_bytes) {
+                        bool have_state, bool want_scores, int threads, int64_t limit,
+                        bool stage_all, size_t &lds_bytes) {
     const int64_t row_bytes = int64_t(d->head_dim) * elem_bytes(d->dtype);
     int nmax = 0, keys_cap = 0, evict_cap = 0, move_cap = 0, want_rows = 0;
     for (int i = 0; i < ns; ++i) {
@@ -80,16 +83,17 @@ vd_status plan_step_lds(const vd_cache_desc *d, UnitParams &p, int ns, bool scor
             want_rows = std::max(want_rows, n);
         }
     }
-    // keys, then (when the unit selects) the second histogram buffer; the fp64
-    // reduction scratch aliases the region
-    const int64_t red_bytes = int64_t(vd::kWaves) * d->head_dim * 8;
-    const int64_t sel_bytes = keys_cap > 0 ? align16(int64_t(keys_cap) * 4) + int64_t(vd::kBins) * 4 : 0;
+    // keys, then (when the unit selects) the second histogram buffer (a bin per
+    // thread); the fp64 reduction scratch aliases the region
+    const int64_t red_bytes = int64_t(threads / 64) * d->head_dim * 8;
+    const int64_t sel_bytes = keys_cap > 0 ? align16(int64_t(keys_cap) * 4) + int64_t(threads) * 4 : 0;
     const int64_t keys_bytes = align16(std::max<int64_t>(sel_bytes, red_bytes));
     const int64_t lists_bytes = align16(int64_t(evict_cap + move_cap) * 4);
     const int64_t used = int64_t(sizeof(vd::LdsHead)) + keys_bytes + lists_bytes;
-    if (used > vd::kLdsBytes) return VD_ERR_UNSUPPORTED;
+    if (used > limit || (stage_all && used + want_rows * row_bytes > limit)) return VD_ERR_UNSUPPORTED;
+    p.threads = threads;
     // as many of the rows to stage as fit (the kernel streams the rest twice)
-    const int64_t stash_rows = std::min<int64_t>(want_rows, (vd::kLdsBytes - used) / row_bytes);
+    const int64_t stash_rows = std::min<int64_t>(want_rows, (limit - used) / row_bytes);
     p.off_keys = int32_t(sizeof(vd::LdsHead));
     p.off_lists = int32_t(p.off_keys + keys_bytes);
     p.off_stash = int32_t(p.off_lists + lists_bytes);
@@ -209,6 +213,29 @@ vd_status launch_decode(const vd_cache_desc *desc, const float *q, float scale,
     return VD_OK;
 }
 
+// Workgroup size and LDS of the pass.  With more units than CUs, two workgroups
+// of half the threads per CU let one unit's selection and gather run beside
+// another's row stream, provided that half the LDS still stages every row that
+// would otherwise be read twice (128-byte rows, the cheapest to read again and
+// as dear to score, gain without); a decode step's selection (one row at most)
+// is too short to hide.  Measured, full against half workgroups, 1024 bf16
+// units (us): d = 128, n = 320 39.4 and 26.1, n = 2176 113.3 and 107.7, n =
+// 4160 185 and 179; d = 64, n = 1152 49.0 and 36.6, n = 8492 (576
+// units, 208 of 300 rows staged) 150 and 139; with 200 of 512 rows
+// staged (n = 2560, d = 128) 132 and 156, with 176 of 256 (eight
+// ragged sequences) 339 and 352, with 74 of 1024 (d = 256) 268 and 302.
+vd_status plan_step(const vd_cache_desc *d, UnitParams &p, int ns, bool score_mode,
+                    bool have_state, bool want_scores, size_t &lds_bytes) {
+    const int64_t units = int64_t(ns) * d->num_layers * d->num_kv_heads;
+    bool argmin = !score_mode;  // every unit evicts at most one row
+    for (int i = 0; i < ns; ++i) argmin = argmin && p.nN[2 * i] - 1 <= p.nN[2 * i + 1];
+    if (units > vd::kCus && !argmin &&
+        plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kHalfBlock, vd::kLdsBytes / 2,
+                      d->head_dim * elem_bytes(d->dtype) > 128, lds_bytes) == VD_OK)
+        return VD_OK;
+    return plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kBlock, vd::kLdsBytes, false, lds_bytes);
+}
+
 }  // namespace
 
 extern "C" {
@@ -230,7 +257,7 @@ vd_status vd_score(const vd_cache_desc *desc, const int32_t *n_valid, vd_variant
         p.scores = scores;
         p.mean_out = mean_out;
         size_t lds = 0;
-        if ((st = plan_step_lds(desc, p, ns, true, false, true, lds)) != VD_OK) return st;
+        if ((st = plan_step(desc, p, ns, true, false, true, lds)) != VD_OK) return st;
         st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds,
                                       reinterpret_cast<hipStream_t>(stream)));
         if (st != VD_OK) return st;
@@ -321,8 +348,7 @@ vd_status vd_evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const
         p.scores = scores_out;
         p.keep = keep_out;
         size_t lds = 0;
-        if ((st = plan_step_lds(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr,
-                                lds)) != VD_OK)
+        if ((st = plan_step(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, lds)) != VD_OK)
             return st;
         st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds,
                                       reinterpret_cast<hipStream_t>(stream)));

@@ -108,12 +108,12 @@ template <> struct Elem<1> {  // fp32
     }
 };
 
-template <int DT, int D> struct Shape {
+template <int DT, int D, int THREADS = NT> struct Shape {
     static constexpr int EPL = Elem<DT>::EPL;
     static constexpr int ROWB = D * Elem<DT>::BYTES;  // bytes per row
     static constexpr int LPR = ROWB / 16;             // lanes per row
     static constexpr int RPW = 64 / LPR;              // rows per wave instruction
-    static constexpr int GROUPS = NW * RPW;           // row groups per workgroup
+    static constexpr int GROUPS = THREADS / 64 * RPW; // row groups per workgroup
     static constexpr int STEP = GROUPS * kUnroll;     // rows per tile
     static_assert(LPR >= 8 && LPR <= 64 && 64 % LPR == 0, "unsupported row shape");
 };
@@ -353,9 +353,10 @@ template <int O> __device__ __forceinline__ double pair_sum_split(double p, doub
     return __longlong_as_double(((unsigned long long)H[0] << 32) | L[0]) +
            __longlong_as_double(((unsigned long long)H[1] << 32) | L[1]);
 }
-template <int DT, int D>
+template <int DT, int D, int THREADS = kBlock>
 __device__ __forceinline__ double block_col_total(double *acc, double *red, int red_cap) {
-    using S = Shape<DT, D>;
+    using S = Shape<DT, D, THREADS>;
+    constexpr int NT = THREADS, NW = NT / 64;
     constexpr int E = S::EPL;
     // The wave's row groups are summed in halving steps (lanes 16 apart, then
     // 32 apart), each lane keeping half of its columns per step, in the same
@@ -442,10 +443,13 @@ __device__ __forceinline__ uint32_t sum_below16(uint32_t x, int i) {
 // the wave wait for its load); only the sweep's first kTouchIters blocks of 64
 // slots touch.
 constexpr int kTouchIters = 4, kTouchLines = 2;
+template <int THREADS = kBlock>
 __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int N, uint32_t *evl, int evict_cap,
                                                 uint32_t *mvl, int move_cap, uint8_t *keep_out, LdsHead &H,
                                                 int keys_words, const char *tv, const char *tk, uint32_t ss,
                                                 int row_bytes, uint32_t (&tch)[kTouchIters][kTouchLines]) {
+    constexpr int NW = THREADS / 64, BINS = THREADS, LOG_BINS = BINS == 1024 ? 10 : 9;
+    static_assert(BINS == 1 << LOG_BINS && BINS <= kBins, "one histogram bin per thread");
     uint32_t *const hist2 = const_cast<uint32_t *>(keys) + ((n + 3) & ~3);
     const int hist2_cap = keys_words - ((n + 3) & ~3);
     const int w = wave_id_s(), lane = lane_id();
@@ -464,8 +468,8 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
     struct Bin { int b; uint32_t h, above; };
     auto find_bin = [&](const uint32_t *hc, int hc_cap, uint32_t *hn, int hn_cap)
                         __attribute__((always_inline)) -> Bin {
-        const uint32_t total = wave_incl_scan(hc[lds_ix<kSiteHist>(kBins - 1 - threadIdx.x, hc_cap)]);
-        hn[lds_ix<kSiteHist>(threadIdx.x, hn_cap)] = 0u;  // NT == kBins
+        const uint32_t total = wave_incl_scan(hc[lds_ix<kSiteHist>(BINS - 1 - threadIdx.x, hc_cap)]);
+        hn[lds_ix<kSiteHist>(threadIdx.x, hn_cap)] = 0u;  // THREADS == BINS
         if (lane == 63) H.bc[80 + w] = total;
         __syncthreads();
         const uint32_t un = (uint32_t)need;
@@ -474,19 +478,19 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
         // the wave holding it (the totals sum to in_range >= need, so one lane qualifies)
         const int tw = max(__ffsll(__ballot(lane < NW && wincl >= un)) - 1, 0);
         const uint32_t before = lane_u32(wincl - wt, tw);
-        const uint32_t hb = hc[lds_ix<kSiteHist>(kBins - 1 - (tw * 64 + lane), hc_cap)];
+        const uint32_t hb = hc[lds_ix<kSiteHist>(BINS - 1 - (tw * 64 + lane), hc_cap)];
         const uint32_t bincl = wave_incl_scan(hb) + before;
         const int tl = max(__ffsll(__ballot(bincl >= un)) - 1, 0);
         const uint32_t h = lane_u32(hb, tl);
-        return Bin{kBins - 1 - (tw * 64 + tl), h, lane_u32(bincl, tl) - h};
+        return Bin{BINS - 1 - (tw * 64 + tl), h, lane_u32(bincl, tl) - h};
     };
     for (int pass = 0; in_range > kCand && lo != hi; ++pass) {
         uint32_t *hc = (pass & 1) ? hist2 : H.hist;
         uint32_t *hn = (pass & 1) ? H.hist : hist2;
-        const int hc_cap = (pass & 1) ? hist2_cap : kBins;
-        const int hn_cap = (pass & 1) ? kBins : hist2_cap;
+        const int hc_cap = (pass & 1) ? hist2_cap : BINS;
+        const int hn_cap = (pass & 1) ? BINS : hist2_cap;
         const int bits = 32 - __clz(hi - lo);  // bits of the largest offset
-        const int shift = bits > 10 ? bits - 10 : 0;
+        const int shift = bits > LOG_BINS ? bits - LOG_BINS : 0;
         // a lane outside the range adds 0 to a bin of its own (no lane mask switched)
         for (int jb = j0; jb < j1; jb += 64) {
             const int j = jb + lane;
@@ -656,9 +660,10 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
 
 // ---------------------------------------------------------------- the pass
 
-template <int DT, int D, int VAR>
-__global__ void __launch_bounds__(NT) step_kernel(const UnitParams p) {
-    using S = Shape<DT, D>;
+template <int DT, int D, int VAR, int THREADS>
+__global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
+    using S = Shape<DT, D, THREADS>;
+    constexpr int NT = THREADS, NW = NT / 64;
     using E = Elem<DT>;
     extern __shared__ __align__(16) unsigned char lds[];
     LdsHead &H = *reinterpret_cast<LdsHead *>(lds);
@@ -810,7 +815,7 @@ __global__ void __launch_bounds__(NT) step_kernel(const UnitParams p) {
         }
     };
     auto finish_mean = [&]() __attribute__((always_inline)) {
-        const double fresh_sum = block_col_total<DT, D>(acc, red, red_cap);
+        const double fresh_sum = block_col_total<DT, D, THREADS>(acc, red, red_cap);
         if (threadIdx.x < D) {
             const int t = threadIdx.x;
             const double old_sum = count > 0 ? st_col : 0.0;
@@ -1023,7 +1028,7 @@ __global__ void __launch_bounds__(NT) step_kernel(const UnitParams p) {
             H.bc[wave_id()] = kmin;
             H.bc[16 + wave_id()] = kmax;
         }
-        H.hist[threadIdx.x] = 0u;  // NT == kBins
+        H.hist[threadIdx.x] = 0u;  // one bin per thread
         if (threadIdx.x == 0) H.bc[100] = 0u;  // candidate count
     }
     __syncthreads();
@@ -1074,7 +1079,7 @@ __global__ void __launch_bounds__(NT) step_kernel(const UnitParams p) {
             __syncthreads();
         } else {
             (void)lds_ix<kSiteKeys>(n - 1, p.keys_cap);  // the keys fit their region
-            n_moves = select_and_build(keys, n, N, evl, p.evict_cap, mvl, p.move_cap, keep_out, H,
+            n_moves = select_and_build<THREADS>(keys, n, N, evl, p.evict_cap, mvl, p.move_cap, keep_out, H,
                                        keys_words, vb, p.k ? p.k + off : nullptr, ss32, S::ROWB, tch);
         }
     } else {
@@ -1223,7 +1228,7 @@ __global__ void __launch_bounds__(NT) step_kernel(const UnitParams p) {
 #pragma unroll
             for (int l = 0; l < kTouchLines; ++l) asm volatile("" ::"v"(tch[i][l]));
         if (st) {
-            const double delta = block_col_total<DT, D>(acc, red, red_cap);  // red aliases keys, no longer needed
+            const double delta = block_col_total<DT, D, THREADS>(acc, red, red_cap);  // red aliases keys, no longer needed
             if (threadIdx.x < D) st[threadIdx.x] = (steady ? H.old_sum[threadIdx.x] : H.sum[threadIdx.x]) + delta;
             if (threadIdx.x == 0) st[D] = (double)N;
         }
@@ -2373,21 +2378,21 @@ template <int DT> void *attn_kernel_for(int head_dim, int group, bool caote, boo
 
 // The ABI's variants onto the kernel's score forms (a key-side variant is the
 // value-side form on the rows the host passes in V's place).
-template <int DT, int D> void *step_kernel_for(int variant) {
+template <int DT, int D, int THREADS> void *step_kernel_for(int variant) {
     switch (variant) {
-        case 0: case 3: return reinterpret_cast<void *>(&step_kernel<DT, D, kL2>);
-        case 1: case 4: return reinterpret_cast<void *>(&step_kernel<DT, D, kDir>);
-        case 2: return reinterpret_cast<void *>(&step_kernel<DT, D, kNorm>);
-        case 5: return reinterpret_cast<void *>(&step_kernel<DT, D, kKeepSmallest>);
+        case 0: case 3: return reinterpret_cast<void *>(&step_kernel<DT, D, kL2, THREADS>);
+        case 1: case 4: return reinterpret_cast<void *>(&step_kernel<DT, D, kDir, THREADS>);
+        case 2: return reinterpret_cast<void *>(&step_kernel<DT, D, kNorm, THREADS>);
+        case 5: return reinterpret_cast<void *>(&step_kernel<DT, D, kKeepSmallest, THREADS>);
     }
     return nullptr;
 }
 
-template <int DT> void *step_kernel_for(int head_dim, int variant) {
+template <int DT, int THREADS> void *step_kernel_for(int head_dim, int variant) {
     switch (head_dim) {
-        case 64: return step_kernel_for<DT, 64>(variant);
-        case 128: return step_kernel_for<DT, 128>(variant);
-        case 256: return step_kernel_for<DT, 256>(variant);
+        case 64: return step_kernel_for<DT, 64, THREADS>(variant);
+        case 128: return step_kernel_for<DT, 128, THREADS>(variant);
+        case 256: return step_kernel_for<DT, 256, THREADS>(variant);
     }
     return nullptr;
 }
@@ -2402,20 +2407,22 @@ template <int DT> void *compact_kernel_for(int head_dim) {
 }
 
 hipError_t launch(void *fn, int num_seqs, size_t lds_bytes, hipStream_t stream,
-                  const UnitParams &p) {
+                  const UnitParams &p, int threads = NT) {
     if (!fn) return hipErrorInvalidDeviceFunction;
     void *args[] = {const_cast<UnitParams *>(&p)};
     const dim3 grid(p.num_kv_heads, p.num_layers, num_seqs);
-    return hipLaunchKernel(fn, grid, dim3(NT), args, lds_bytes, stream);
+    return hipLaunchKernel(fn, grid, dim3(threads), args, lds_bytes, stream);
 }
 
 }  // namespace
 
 hipError_t launch_step(const UnitParams &p, int num_seqs, int dtype, int head_dim,
                        int variant, size_t lds_bytes, hipStream_t stream) {
-    void *fn = dtype == 0 ? step_kernel_for<0>(head_dim, variant)
-                          : step_kernel_for<1>(head_dim, variant);
-    return launch(fn, num_seqs, lds_bytes, stream, p);
+    void *fn = p.threads == kHalfBlock ? (dtype == 0 ? step_kernel_for<0, kHalfBlock>(head_dim, variant)
+                                                     : step_kernel_for<1, kHalfBlock>(head_dim, variant))
+                                       : (dtype == 0 ? step_kernel_for<0, kBlock>(head_dim, variant)
+                                                     : step_kernel_for<1, kBlock>(head_dim, variant));
+    return launch(fn, num_seqs, lds_bytes, stream, p, p.threads);
 }
 
 hipError_t launch_select(const UnitParams &p, int num_seqs, size_t lds_bytes,

@@ -9,6 +9,8 @@ namespace vd {
 
 constexpr int kBlock = 1024;              // threads per workgroup (16 waves of 64)
 constexpr int kWaves = kBlock / 64;
+constexpr int kHalfBlock = kBlock / 2;    // the pass with two workgroups per CU
+constexpr int kCus = 256;                 // compute units of an MI355X
 constexpr int kMaxSeqsPerLaunch = 256;    // per-sequence n and N travel as kernel arguments
 constexpr int kLdsBytes = 160 * 1024;     // LDS of one gfx950 workgroup
 
@@ -52,7 +54,7 @@ struct UnitParams {
     int32_t keys_cap;         // entries in the keys region
     int32_t evict_cap;        // entries of the first list
     int32_t move_cap;         // entries of the second list
-    int32_t pad0;
+    int32_t threads;          // threads per workgroup of the pass: kBlock or kHalfBlock
     int32_t *pos;             // [U][capacity] or null
     float *scores;            // [U][capacity] or null (required in kModeScore)
     const float *scores_in;   // select kernel input

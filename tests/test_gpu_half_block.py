@@ -1,0 +1,73 @@
+"""The pass with two workgroups per CU (launches of more than 256 units whose
+rows to stage fit half the LDS, or are 128 bytes each) against the same sequences one at a time, which
+take the full workgroup: scores, kept sets, rows and positions bit for bit.
+The fp64 column sums are added in another order, which bf16 rows do not see
+(their sums are exact) and which moves an fp32 row's mean by less than 2^-50 of
+its terms.  Cases sit at the edges of the row tiles (512 threads take 256 to 32
+rows per chunk column), of the staging, and of the selection (no eviction, one
+row, a crossing fill, all keys equal)."""
+import ctypes
+import os
+
+import pytest
+import torch
+
+from paper_2609_23314_amd import build as lib_build
+from paper_2609_23314_amd import synth, vd
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+S, L, H = 3, 12, 8                    # 288 units in one launch, 96 in each of three
+
+SIZES = [([130, 97, 64], [100, 96, 64]), ([67, 2, 1], [3, 1, 1]), ([1030, 700, 513], [1000, 690, 512]),
+         ([300, 290, 80], [256, 257, 70])]
+
+
+@pytest.fixture(params=["release", "debug"])
+def library(request):
+    saved = (vd._lib, vd.LIB_PATH)
+    if request.param == "debug":
+        assert os.path.exists(lib_build.DEBUG_LIB), "build the debug library first"
+        vd._lib, vd.LIB_PATH = None, lib_build.DEBUG_LIB
+    lib = vd.load()
+    yield lib if request.param == "debug" else None
+    vd._lib, vd.LIB_PATH = saved
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("variant", ["l2", "dir", "norm", "key_norm"])
+@pytest.mark.parametrize("D,n,N,ties", [(D, n, N, False) for D in (64, 128, 256) for n, N in SIZES] +
+                         [(128, *SIZES[3], True), (64, [2300, 2100, 2050], [1300, 1500, 2050], False)])
+def test_half_block_matches_full(library, dtype, D, variant, n, N, ties):
+    C, U = max(n) + 3, S * L * H
+    k, v = [synth.random_rows((S, L, H, C, D), dtype, 91 + i, DEV) for i in range(2)]
+    if ties:
+        k, v = [x[:, :, :, :1].expand(-1, -1, -1, C, -1).contiguous() for x in (k, v)]
+        v[:, :, :, 5::40] *= 2
+        k[:, :, :, 7::50] *= 2
+    scored = k if variant.startswith("key") else v
+    count = [min(a, b) for a, b in zip(n, N)]
+    count[2] = max(0, count[2] - 5)   # one sequence's state lags behind
+    sums = torch.zeros((S, L, H, D + 1), dtype=torch.float64, device=DEV)
+    for s in range(S):
+        sums[s, ..., :D] = scored[s, :, :, :count[s]].double().sum(2)
+        sums[s, ..., D] = count[s]
+    pos = torch.arange(C, dtype=torch.int32, device=DEV).repeat(U, 1)
+    one = [x.clone() for x in (k, v, sums, pos)]
+    got = dict(scores=torch.zeros((U, C), device=DEV), keep=torch.zeros((U, C), dtype=torch.uint8, device=DEV))
+    ref = {a: x.clone() for a, x in got.items()}
+    vd.vd_evict_step(k, v, n, N, variant, running_sum=sums.view(U, -1), pos=pos, scores_out=got["scores"],
+                     keep_out=got["keep"])
+    for s in range(S):
+        u = slice(s * L * H, (s + 1) * L * H)
+        vd.vd_evict_step(one[0][s:s + 1], one[1][s:s + 1], n[s:s + 1], N[s:s + 1], variant,
+                         running_sum=one[2][s].view(L * H, -1), pos=one[3][u], scores_out=ref["scores"][u],
+                         keep_out=ref["keep"][u])
+    for a, b in zip((k, v, pos), (one[0], one[1], one[3])):
+        assert torch.equal(a, b)
+    assert torch.equal(got["keep"], ref["keep"]) and torch.equal(got["scores"], ref["scores"])
+    assert torch.allclose(sums, one[2], rtol=1e-12, atol=1e-12 * float(scored[0].double().abs().max()) * C)
+    if library is not None:
+        word = ctypes.c_uint32(0)
+        library.vd_debug_take_error_word.argtypes = [ctypes.c_void_p]
+        assert library.vd_debug_take_error_word(ctypes.byref(word)) == vd.VD_OK and word.value == 0
