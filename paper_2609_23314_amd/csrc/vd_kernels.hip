@@ -1660,7 +1660,9 @@ constexpr int kAttnRows = 2;           // rows per lane group in one tile of the
 // every weight 2^(z - reference) stays at most 2^8 and most tiles leave the
 // running sums unscaled.  The merges take each part's reference, whatever it is.
 constexpr float kLazyLog2 = 8.0f;
-constexpr int kMergeBatch = 8;  // splits whose partials the combine loads at once
+constexpr int kMergeBatch = 8;  // splits whose partials a thread of the combine loads at once
+constexpr int kCombineThreads = 1024;
+constexpr int kMaxSplits = 64;  // one lane of the combine per split (the host plans no more)
 
 template <int DT, int D> struct AttnShape {
     static constexpr int EPL = Elem<DT>::EPL;
@@ -1696,9 +1698,11 @@ __device__ __forceinline__ int state_count(const double *st, int n) {
 
 // CAOTE: the FastCAOTE variant (App. A, Eq. app_fastcaote), whose score needs
 // every row's weight under the merged softmax: each row's G logits (log2
-// units) and its distance to the mean are kept in LDS, rows[(e - r0) * (G+1)
-// + g] and [.. + G], and written to the workspace at the split's end, for the
-// combine kernel to score once the splits' maxima and sums are merged.
+// units) and its distance to the mean are kept in LDS, one plane of split_rows
+// words per head and one for the distances, and written to the workspace at
+// the split's end (planes of capacity words, so that the combine kernel's
+// lanes read consecutive words), for it to score once the splits' maxima and
+// sums are merged.
 template <int DT, int D, int G, bool CAOTE>
 __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitParams p) {
     using A = AttnShape<DT, D>;
@@ -1861,8 +1865,8 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
 #pragma unroll
                 for (int h = 0; h < NQ; ++h)
                     if (G != 1 || !odd)
-                        rows[lds_ix<kSiteRows>((e - r0) * (G + 1) + hq[h], p.split_rows * (G + 1))] = zq[h];
-                if (!odd) rows[lds_ix<kSiteRows>((e - r0) * (G + 1) + G, p.split_rows * (G + 1))] = dist;
+                        rows[lds_ix<kSiteRows>(hq[h] * p.split_rows + e - r0, p.split_rows * (G + 1))] = zq[h];
+                if (!odd) rows[lds_ix<kSiteRows>(G * p.split_rows + e - r0, p.split_rows * (G + 1))] = dist;
             }
         } else {
             const uint32_t key = score_key(dist);
@@ -2016,8 +2020,8 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
                     if (cl == 0 && valid[r]) {
 #pragma unroll
                         for (int g = 0; g < G; ++g)
-                            rows[lds_ix<kSiteRows>((e - r0) * (G + 1) + g, p.split_rows * (G + 1))] = z[r][g];
-                        rows[lds_ix<kSiteRows>((e - r0) * (G + 1) + G, p.split_rows * (G + 1))] = dist;
+                            rows[lds_ix<kSiteRows>(g * p.split_rows + e - r0, p.split_rows * (G + 1))] = z[r][g];
+                        rows[lds_ix<kSiteRows>(G * p.split_rows + e - r0, p.split_rows * (G + 1))] = dist;
                     }
                 } else {
                     const uint32_t key = score_key(dist);
@@ -2116,10 +2120,11 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
         p.ws_amin[wsi] = m;
     }
     if constexpr (CAOTE) {  // the rows' logits and distances (written before the barrier above)
-        const int cnt = max(r1 - r0, 0) * (G + 1);
-        float *dst = p.ws_rows + (u * p.capacity + r0) * (G + 1);
-        for (int i = threadIdx.x; i < cnt; i += kAttnThreads)
-            dst[i] = rows[lds_ix<kSiteRows>(i, p.split_rows * (G + 1))];
+        float *dst = p.ws_rows + u * p.capacity * (G + 1) + r0;
+#pragma unroll
+        for (int g = 0; g <= G; ++g)
+            for (int i = threadIdx.x; i < r1 - r0; i += kAttnThreads)
+                dst[g * p.capacity + i] = rows[lds_ix<kSiteRows>(g * p.split_rows + i, p.split_rows * (G + 1))];
     }
 }
 
@@ -2128,87 +2133,100 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
 // ~slot), the lowest score and the highest slot among equal ones: a_j = (1/G)
 // sum_g 2^(z_gj - M_g) / L_g with M_g, L_g the merged maximum and weight sum
 // of head g, 1 - a_j = (1/G) sum_g (L_g - w_gj) / L_g (a row that holds all
-// of a head's weight scores +infinity).  Every thread of the block takes part
-// and receives the minimum; `ml` is the unit's [S][G][2] split maxima and sums.
-template <int G>
-__device__ __forceinline__ unsigned long long caote_argmin(const UnitParams &p, int64_t u, int n,
-                                                           const float *ml, int S) {
-    __shared__ float mg[G], lg[G];
-    __shared__ unsigned long long wbest[kAttnWaves];
-    // kRowsAtOnce rows per thread at a time, all their words read before any
-    // is used (one memory round trip per batch; n = 4097 is one batch), the
-    // first batch before the heads' maxima and sums are merged
-    constexpr int kRowsAtOnce = 17;
-    const float *rows = p.ws_rows + u * p.capacity * (G + 1);
+// of a head's weight scores +infinity).  Rows are taken kRowsAtOnce per thread
+// at a time, all their words read before any is used (one memory round trip
+// per batch; up to 5120 rows are one batch); the caller has read the first batch.
+constexpr int kRowsAtOnce = 5;
+template <int G, int T> struct CaoteRows {
     float x[kRowsAtOnce][G + 1];
-    auto load_rows = [&](int j0) __attribute__((always_inline)) {
+    __device__ __forceinline__ void load(const float *rows, int64_t plane, int j0, int n) {
 #pragma unroll
         for (int r = 0; r < kRowsAtOnce; ++r) {
-            const int j = min(j0 + r * kAttnThreads, n - 1);  // past the end: row n - 1 again, unused
+            const int j = min(j0 + r * T, n - 1);  // past the end: row n - 1 again, unused
 #pragma unroll
-            for (int g = 0; g <= G; ++g) x[r][g] = rows[j * (G + 1) + g];
+            for (int g = 0; g <= G; ++g) x[r][g] = rows[g * plane + j];
         }
-    };
-    load_rows(threadIdx.x);
-    if (threadIdx.x < G) {
-        // the splits in batches of kMergeBatch whose loads all go out together
-        // (a split past S reads split s0 again and weighs 0), each batch
-        // raising the running reference to its largest logit
-        const int g = threadIdx.x;
-        float top = kNoLogit, den = 0.f;
-        for (int s0 = 0; s0 < S; s0 += kMergeBatch) {
-            float m[kMergeBatch], l[kMergeBatch];
+    }
+    __device__ __forceinline__ unsigned long long lowest(const float *rows, int64_t plane, int n, const float *mg,
+                                                         const float *lg) {
+        float M[G], Lw[G], inv[G];
 #pragma unroll
-            for (int i = 0; i < kMergeBatch; ++i) {
-                const int s = s0 + i < S ? s0 + i : s0;
-                m[i] = ml[(s * G + g) * 2];
-                l[i] = ml[(s * G + g) * 2 + 1];
+        for (int g = 0; g < G; ++g) {
+            M[g] = mg[g];
+            Lw[g] = lg[g];
+            inv[g] = 1.f / Lw[g];
+        }
+        unsigned long long best = ~0ull;
+        for (int j0 = threadIdx.x; j0 < n; j0 += kRowsAtOnce * T) {
+            if (j0 != (int)threadIdx.x) load(rows, plane, j0, n);
+#pragma unroll
+            for (int r = 0; r < kRowsAtOnce; ++r) {
+                const int j = j0 + r * T;
+                float a = 0.f, rest = 0.f;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const float w = __builtin_amdgcn_exp2f(x[r][g] - M[g]);
+                    a = fmaf(w, inv[g], a);
+                    rest = fmaf(fmaxf(Lw[g] - w, 0.f), inv[g], rest);
+                }
+                const float sc = rest > 0.f ? (a / rest) * x[r][G] : __builtin_inff();  // the 1/G cancels
+                const unsigned long long k = ((unsigned long long)score_key(sc) << 32) | (uint32_t)~(uint32_t)j;
+                best = j < n && k < best ? k : best;
             }
-            float bt = top;
-#pragma unroll
-            for (int i = 0; i < kMergeBatch; ++i) bt = fmaxf(bt, m[i]);
-            if (s0 > 0) den *= __builtin_amdgcn_exp2f(top - bt);
-            top = bt;
-#pragma unroll
-            for (int i = 0; i < kMergeBatch; ++i)
-                if (s0 + i < S) den += l[i] * __builtin_amdgcn_exp2f(m[i] - top);
         }
-        mg[threadIdx.x] = top;
-        lg[threadIdx.x] = den;
+        return best;
     }
-    __syncthreads();
-    float M[G], Lw[G], inv[G];
+};
+
+__device__ __forceinline__ float wave_max_f32(float x) {
+    x = fmaxf(x, dpp<0xB1>(x));
+    x = fmaxf(x, dpp<0x4E>(x));
+    x = fmaxf(x, dpp<0x141>(x));
+    x = fmaxf(x, dpp<0x140>(x));
+    x = fmaxf(x, __shfl_xor(x, 16));
+    return fmaxf(x, __shfl_xor(x, 32));
+}
+
+// The eviction of the combine kernels by LPR lanes, lane c owning the columns
+// of chunk c of a row: the running sum takes the rows it did not cover and
+// loses the evicted row j (its chunk xj, read before the move overwrites it,
+// so no barrier is needed), and the newest row (kl, vl, pl) fills the hole.
+// cnt, old: the state's count and this lane's columns of its sums.
+template <int DT, int D>
+__device__ __forceinline__ void evict_row(const UnitParams &p, int64_t u, char *kb, char *vb, double *st, double cnt,
+                                          const double (&old)[AttnShape<DT, D>::EPL], uint4 kl, uint4 vl, int32_t pl,
+                                          uint4 xj, int c, int j, int n, int N) {
+    using E = Elem<DT>;
+    constexpr int EPL = AttnShape<DT, D>::EPL;
+    const uint32_t ss32 = p.s_slot;
+    const int last = n > 0 ? n - 1 : 0;
+    const int count = (cnt >= 0.0 && cnt <= (double)n && cnt == (double)(int)cnt) ? (int)cnt : 0;
+    // the rows the state does not cover, in slot order (the newest one is loaded)
+    double sum[EPL], f[EPL];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        M[g] = mg[g];
-        Lw[g] = lg[g];
-        inv[g] = 1.f / Lw[g];
+    for (int i = 0; i < EPL; ++i) f[i] = 0.0;
+    for (int r = count; r < n; ++r) {
+        float x[EPL];
+        E::unpack(r == last ? vl : load_stream(vb, row_off(r, ss32, c)), x);
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) f[i] += (double)x[i];
     }
-    unsigned long long best = ~0ull;
-    for (int j0 = threadIdx.x; j0 < n; j0 += kRowsAtOnce * kAttnThreads) {
-        if (j0 != (int)threadIdx.x) load_rows(j0);
 #pragma unroll
-        for (int r = 0; r < kRowsAtOnce; ++r) {
-            const int j = j0 + r * kAttnThreads;
-            float a = 0.f, rest = 0.f;
+    for (int i = 0; i < EPL; ++i) sum[i] = (count > 0 ? old[i] : 0.0) + f[i];
+    if (j >= 0) {  // the evicted row leaves the running sum
+        float x[EPL];
+        E::unpack(xj, x);
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float w = __builtin_amdgcn_exp2f(x[r][g] - M[g]);
-                a = fmaf(w, inv[g], a);
-                rest = fmaf(fmaxf(Lw[g] - w, 0.f), inv[g], rest);
-            }
-            const float sc = rest > 0.f ? (a / rest) * x[r][G] : __builtin_inff();  // the 1/G cancels
-            const unsigned long long k = ((unsigned long long)score_key(sc) << 32) | (uint32_t)~(uint32_t)j;
-            best = j < n && k < best ? k : best;
-        }
+        for (int i = 0; i < EPL; ++i) sum[i] -= (double)x[i];
     }
-    best = wave_min_u64(best);
-    if (lane_id() == 0) wbest[wave_id()] = best;
-    __syncthreads();
-    unsigned long long m = ~0ull;
 #pragma unroll
-    for (int q = 0; q < kAttnWaves; ++q) m = wbest[q] < m ? wbest[q] : m;
-    return m;
+    for (int i = 0; i < EPL; ++i) st[c * EPL + i] = sum[i];
+    if (c == 0) st[D] = (double)(n > N ? N : n);
+    if (j >= 0 && j < N) {  // slot reuse: the newest kept row N (= n - 1) fills the hole
+        store_stream(kb, row_off(j, ss32, c), kl);
+        store_stream(vb, row_off(j, ss32, c), vl);
+        if (p.pos && c == 0) p.pos[u * p.capacity + j] = pl;
+    }
 }
 
 // Merges a unit's splits into the attention output of its G query rows, then
@@ -2217,18 +2235,145 @@ __device__ __forceinline__ unsigned long long caote_argmin(const UnitParams &p, 
 // slot below N (slot reuse) and updates the running sum.  Launched after the
 // split kernel, so every row has been read before anything moves.
 //
+// A chain of memory round trips, one workgroup per unit, so the work is spread
+// for few trips: wave g takes head g's split maxima and sums, one split per
+// lane, and leaves every split's factor 2^(m_s - M_g) in LDS; the G * D output
+// columns times kParts parts of the splits give every thread one column of one
+// part (the splits s = part, part + kParts, ...), kMergeBatch loads of the
+// partial outputs in flight, the first batch issued before the factors are
+// known; the parts meet in LDS.  With one thread per column, eight splits at a
+// time, and a FastCAOTE row's words 20 bytes apart this took (us, now in
+// brackets): 16 units of 48 splits, d = 256, G = 2 9.9 [6.1]; 8 units of 64
+// splits, d = 128, G = 4 10.2 [6.2], with FastCAOTE at n = 8193 21.5 [11.9];
+// 128 units of 6 splits with FastCAOTE at n = 4097 9.3 [8.6].
+//
 // The eviction is the work of LPR lanes of the last wave, lane c owning the
 // columns of chunk c of a row.  Every lane of the block loads its state
 // columns, its chunk of the newest row (row N when evicting) and the argmin
-// words at once (lanes outside the eviction read chunk 0); only the evicted
-// row's chunk waits for the argmin, and it goes out with the loads of the
-// split partials, so that the block waits for memory twice.  Each lane reads
-// its chunk of the evicted row before it overwrites it, so no barrier is
-// needed.
+// words at once (lanes outside the eviction read chunk 0, so that no loaded
+// value leaves a branch); only the evicted row's chunk waits for the argmin.
+// Each lane reads its chunk of the evicted row before it overwrites it, so no
+// barrier is needed.
 template <int DT, int D, int G, bool CAOTE>
-__global__ void __launch_bounds__(kAttnThreads) attn_combine_kernel(const UnitParams p) {
+__global__ void __launch_bounds__(kCombineThreads) attn_combine_kernel(const UnitParams p) {
     using A = AttnShape<DT, D>;
-    using E = Elem<DT>;
+    constexpr int EPL = A::EPL, LPR = A::LPR;
+    constexpr int T = kCombineThreads, COLS = G * D, kParts = T / COLS;
+    static_assert(T % COLS == 0 && T / 64 >= G && D % 64 == 0, "a wave holds columns of one head");
+    __shared__ float fac[kMaxSplits * G], mg[G], lg[G], part[kParts > 1 ? T : 1];
+    __shared__ unsigned long long wbest[T / 64];
+    const int head = blockIdx.x;
+    const int sl = blockIdx.y / p.num_layers, layer = blockIdx.y % p.num_layers;
+    const int ul = (sl * p.num_layers + layer) * p.num_kv_heads + head;
+    const int64_t u = (int64_t)p.unit0 + ul;
+    const int n = p.nN[2 * sl], N = p.nN[2 * sl + 1];
+    const int64_t off = (int64_t)sl * p.s_seq + (int64_t)layer * p.s_layer + (int64_t)head * p.s_head;
+    char *kb = p.k + off;
+    char *vb = p.v + off;
+    const uint32_t ss32 = p.s_slot;
+    double *st = p.running_sum + u * (D + 1);
+    const int S = p.splits;
+    const bool evict = n > N;  // the host admits n <= N + 1 only
+    constexpr int kEvWave = T / 64 - 1;
+    static_assert(LPR <= 64, "the chunks of a row fit one wave");
+    const int c = threadIdx.x - kEvWave * 64;
+    const bool ev = c >= 0 && c < LPR;
+    const int ce = ev ? c : 0;
+    const int last = n > 0 ? n - 1 : 0;
+    const int w = wave_id_s(), lane = lane_id();
+
+    // the partial outputs of this thread's column and splits, first batch
+    const int col = threadIdx.x % COLS, pt = threadIdx.x / COLS, g = col / D;
+    const float *pa = p.ws_acc + u * S * COLS + col;
+    float a[kMergeBatch];
+    auto load_part = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kMergeBatch; ++i) {
+            const int s = s0 + i * kParts;
+            a[i] = pa[(s < S ? s : 0) * COLS];  // past the end: split 0, weighed 0
+        }
+    };
+    load_part(pt);
+    const float *ml = p.ws_ml + u * S * G * 2;
+    const int hl = min(w, G - 1), sp = min(lane, S - 1);  // head and split of this lane in the merge
+    const float m = ml[(sp * G + hl) * 2], l = ml[(sp * G + hl) * 2 + 1];
+    unsigned long long lowest = ~0ull;
+    if constexpr (!CAOTE) lowest = p.ws_amin[u * S + sp];
+    CaoteRows<G, T> cr;
+    const float *rows = p.ws_rows + u * p.capacity * (G + 1);
+    if constexpr (CAOTE) cr.load(rows, p.capacity, threadIdx.x, max(n, 1));
+    const double cnt = st[D];
+    double old[EPL];
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) old[i] = st[ce * EPL + i];
+    const uint4 kl = load_stream(kb, row_off(last, ss32, ce));
+    const uint4 vl = load_stream(vb, row_off(last, ss32, ce));
+    // row N's position (any readable word when there is none to move), by a
+    // vector load (the index in VGPRs), so that no wait for it comes early
+    const bool has_pos = p.pos && evict;
+    const int32_t *pbase = has_pos ? p.pos : reinterpret_cast<const int32_t *>(kb);
+    int64_t pix = has_pos ? u * p.capacity + N : 0;
+    asm volatile("" : "+v"(pix));
+    const int32_t pl = pbase[pix];
+
+    if (w < G) {
+        const float top = wave_max_f32(m);  // (the lanes past S hold split S - 1 again)
+        const float f = __builtin_amdgcn_exp2f(m - top);
+        float den = lane < S ? l * f : 0.f;
+        den = row_sum<64>(den);
+        if (lane < S) fac[lane * G + w] = f;
+        if (lane == 0) {
+            mg[w] = top;
+            lg[w] = den;
+        }
+    }
+    __syncthreads();
+    if constexpr (CAOTE) {
+        if (evict) {  // uniform branch
+            const unsigned long long best = wave_min_u64(cr.lowest(rows, p.capacity, n, mg, lg));
+            if (lane == 0) wbest[w] = best;
+            __syncthreads();
+            lowest = lane < T / 64 ? wbest[lane] : ~0ull;
+        }
+    }
+    lowest = wave_min_u64(lowest);
+    const int j = evict ? (int)~(uint32_t)lowest : -1;
+    const uint4 xj = load_stream(vb, row_off(j >= 0 ? j : 0, ss32, ce));  // used after the outputs
+
+    float num = 0.f;
+    for (int s0 = pt; s0 < S; s0 += kMergeBatch * kParts) {
+        if (s0 != pt) load_part(s0);
+#pragma unroll
+        for (int i = 0; i < kMergeBatch; ++i) {
+            const int s = s0 + i * kParts;
+            const float f = fac[min(s, S - 1) * G + g];
+            num = s < S ? fmaf(a[i], f, num) : num;
+        }
+    }
+    if constexpr (kParts > 1) {
+        part[threadIdx.x] = num;
+        __syncthreads();
+        num = 0.f;
+        if (threadIdx.x < COLS)
+#pragma unroll
+            for (int i = 0; i < kParts; ++i) num += part[i * COLS + threadIdx.x];
+    }
+    if (threadIdx.x < COLS) {
+        float *orow = p.attn_out + (((int64_t)sl * p.num_layers + layer) * p.num_kv_heads + head) * COLS;
+        orow[threadIdx.x] = n > 0 ? num / lg[g] : 0.f;
+    }
+    if (ev)
+        evict_row<DT, D>(p, u, kb, vb, st, cnt, old, kl, vl, pl, xj, c, j, n, N);
+}
+
+// The same for at most kMergeBatch splits and ValueDiff: every thread reads its
+// columns' partials and the head's maxima and sums of all splits at once and
+// needs nothing from the others, so the block waits for memory twice (the
+// argmin words, then the evicted row) and for no barrier.  decode_b16's layer
+// call (128 units, six splits) takes 5.1 us here, 6.3 us above.
+template <int DT, int D, int G>
+__global__ void __launch_bounds__(kAttnThreads) attn_combine_few_kernel(const UnitParams p) {
+    using A = AttnShape<DT, D>;
     constexpr int EPL = A::EPL, LPR = A::LPR;
     constexpr int kOut = (G * D + kAttnThreads - 1) / kAttnThreads;  // outputs per thread
     const int head = blockIdx.x;
@@ -2243,13 +2388,6 @@ __global__ void __launch_bounds__(kAttnThreads) attn_combine_kernel(const UnitPa
     double *st = p.running_sum + u * (D + 1);
     const int S = p.splits;
     const bool evict = n > N;  // the host admits n <= N + 1 only
-    // The eviction lanes: the first LPR lanes of the last wave, lane c owning
-    // chunk c of a row.  Every lane loads (the others chunk 0, so that no
-    // loaded value leaves a branch): first what does not depend on the evicted
-    // slot, then the lowest (key, ~slot), from the splits' argmin words (one
-    // per lane, the minimum taken by each wave) or, for FastCAOTE, from every
-    // row's score; the evicted row's chunk then goes out with the output
-    // loads below.
     constexpr int kEvWave = kAttnWaves - 1;
     static_assert(LPR <= 64, "the chunks of a row fit one wave");
     const int c = threadIdx.x - kEvWave * 64;
@@ -2269,18 +2407,9 @@ __global__ void __launch_bounds__(kAttnThreads) attn_combine_kernel(const UnitPa
     int64_t pix = has_pos ? u * p.capacity + N : 0;
     asm volatile("" : "+v"(pix));
     const int32_t pl = pbase[pix];
-    unsigned long long lowest = ~0ull;
-    if constexpr (CAOTE) {
-        if (evict) lowest = caote_argmin<G>(p, u, n, p.ws_ml + u * S * G * 2, S);  // uniform branch
-    } else {
-        for (int s = lane_id(); s < S; s += 64) lowest = p.ws_amin[u * S + s] < lowest ? p.ws_amin[u * S + s] : lowest;
-        lowest = wave_min_u64(lowest);
-    }
+    const unsigned long long lowest = wave_min_u64(p.ws_amin[u * S + min(lane_id(), S - 1)]);
     const int j = evict ? (int)~(uint32_t)lowest : -1;
     const uint4 xj = load_stream(vb, row_off(j >= 0 ? j : 0, ss32, ce));  // used after the outputs
-    // outputs: the splits in batches of kMergeBatch whose loads all go out
-    // together (a split past S reads split s0 again and weighs 0), each batch
-    // raising the running reference to its largest logit
     float *orow = p.attn_out + (((int64_t)sl * p.num_layers + layer) * p.num_kv_heads + head) * G * D;
     const float *ml = p.ws_ml + u * S * G * 2;
     const float *pa = p.ws_acc + u * S * G * D;
@@ -2289,89 +2418,52 @@ __global__ void __launch_bounds__(kAttnThreads) attn_combine_kernel(const UnitPa
         const int idx = threadIdx.x + o * kAttnThreads;
         if (idx < G * D) {
             const int g = idx / D, cc = idx % D;
-            float top = kNoLogit, num = 0.f, den = 0.f;
-            for (int s0 = 0; s0 < S; s0 += kMergeBatch) {
-                float m[kMergeBatch], l[kMergeBatch], a[kMergeBatch];
+            float m[kMergeBatch], l[kMergeBatch], a[kMergeBatch], num = 0.f, den = 0.f;
 #pragma unroll
-                for (int i = 0; i < kMergeBatch; ++i) {
-                    const int s = s0 + i < S ? s0 + i : s0;
-                    m[i] = ml[(s * G + g) * 2];
-                    l[i] = ml[(s * G + g) * 2 + 1];
-                    a[i] = pa[(s * G + g) * D + cc];
-                }
-                float bt = top;
+            for (int i = 0; i < kMergeBatch; ++i) {
+                const int s = i < S ? i : 0;
+                m[i] = ml[(s * G + g) * 2];
+                l[i] = ml[(s * G + g) * 2 + 1];
+                a[i] = pa[(s * G + g) * D + cc];
+            }
+            float top = kNoLogit;
 #pragma unroll
-                for (int i = 0; i < kMergeBatch; ++i) bt = fmaxf(bt, m[i]);
-                if (s0 > 0) {  // the earlier batches' sums to the new reference
-                    const float r = __builtin_amdgcn_exp2f(top - bt);
-                    num *= r;
-                    den *= r;
-                }
-                top = bt;
+            for (int i = 0; i < kMergeBatch; ++i) top = fmaxf(top, m[i]);
 #pragma unroll
-                for (int i = 0; i < kMergeBatch; ++i) {
-                    const float f = s0 + i < S ? __builtin_amdgcn_exp2f(m[i] - top) : 0.f;
-                    num = fmaf(a[i], f, num);
-                    den = fmaf(l[i], f, den);
-                }
+            for (int i = 0; i < kMergeBatch; ++i) {
+                const float f = i < S ? __builtin_amdgcn_exp2f(m[i] - top) : 0.f;
+                num = fmaf(a[i], f, num);
+                den = fmaf(l[i], f, den);
             }
             orow[g * D + cc] = n > 0 ? num / den : 0.f;
         }
     }
-    if (ev) {
-        const int count = (cnt >= 0.0 && cnt <= (double)n && cnt == (double)(int)cnt) ? (int)cnt : 0;
-        // the rows the state does not cover, in slot order (the newest one is loaded)
-        double f[EPL];
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) f[i] = 0.0;
-        for (int r = count; r < n; ++r) {
-            float x[EPL];
-            E::unpack(r == last ? vl : load_stream(vb, row_off(r, ss32, c)), x);
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) f[i] += (double)x[i];
-        }
-        double part[EPL];
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) part[i] = (count > 0 ? old[i] : 0.0) + f[i];
-        // the evicted row leaves the running sum; lane c read its chunk before
-        // the move below overwrites it
-        if (j >= 0) {
-            float x[EPL];
-            E::unpack(xj, x);
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) part[i] -= (double)x[i];
-        }
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) st[c * EPL + i] = part[i];
-        if (c == 0) st[D] = (double)(evict ? N : n);
-        if (j >= 0 && j < N) {  // slot reuse: the newest kept row N (= n - 1) fills the hole
-            store_stream(kb, row_off(j, ss32, c), kl);
-            store_stream(vb, row_off(j, ss32, c), vl);
-            if (p.pos && c == 0) p.pos[u * p.capacity + j] = pl;
-        }
-    }
+    if (ev)
+        evict_row<DT, D>(p, u, kb, vb, st, cnt, old, kl, vl, pl, xj, c, j, n, N);
 }
 
-template <int DT, int D, int G> void *attn_kernel_for(bool caote, bool combine) {
+// Kernels of the fused decode step; the combine for `splits` splits.
+template <int DT, int D, int G> void *attn_kernel_for(bool caote, bool combine, int splits) {
     if (caote)
         return combine ? reinterpret_cast<void *>(&attn_combine_kernel<DT, D, G, true>)
                        : reinterpret_cast<void *>(&attn_split_kernel<DT, D, G, true>);
-    return combine ? reinterpret_cast<void *>(&attn_combine_kernel<DT, D, G, false>)
-                   : reinterpret_cast<void *>(&attn_split_kernel<DT, D, G, false>);
+    if (!combine) return reinterpret_cast<void *>(&attn_split_kernel<DT, D, G, false>);
+    return splits <= kMergeBatch ? reinterpret_cast<void *>(&attn_combine_few_kernel<DT, D, G>)
+                                 : reinterpret_cast<void *>(&attn_combine_kernel<DT, D, G, false>);
 }
-template <int DT, int D> void *attn_kernel_for(int group, bool caote, bool combine) {
+template <int DT, int D> void *attn_kernel_for(int group, bool caote, bool combine, int splits) {
     switch (group) {
-        case 1: return attn_kernel_for<DT, D, 1>(caote, combine);
-        case 2: return attn_kernel_for<DT, D, 2>(caote, combine);
-        case 4: return attn_kernel_for<DT, D, 4>(caote, combine);
+        case 1: return attn_kernel_for<DT, D, 1>(caote, combine, splits);
+        case 2: return attn_kernel_for<DT, D, 2>(caote, combine, splits);
+        case 4: return attn_kernel_for<DT, D, 4>(caote, combine, splits);
     }
     return nullptr;
 }
-template <int DT> void *attn_kernel_for(int head_dim, int group, bool caote, bool combine) {
+template <int DT> void *attn_kernel_for(int head_dim, int group, bool caote, bool combine, int splits) {
     switch (head_dim) {
-        case 64: return attn_kernel_for<DT, 64>(group, caote, combine);
-        case 128: return attn_kernel_for<DT, 128>(group, caote, combine);
-        case 256: return attn_kernel_for<DT, 256>(group, caote, combine);
+        case 64: return attn_kernel_for<DT, 64>(group, caote, combine, splits);
+        case 128: return attn_kernel_for<DT, 128>(group, caote, combine, splits);
+        case 256: return attn_kernel_for<DT, 256>(group, caote, combine, splits);
     }
     return nullptr;
 }
@@ -2490,17 +2582,18 @@ hipError_t launch_geometry(const UnitParams &p, int num_seqs, int dtype, int hea
 
 hipError_t launch_attn(const UnitParams &p, int num_seqs, int dtype, int head_dim, int group,
                        bool caote, size_t split_lds, hipStream_t stream) {
-    void *fs = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, false)
-                          : attn_kernel_for<1>(head_dim, group, caote, false);
-    void *fc = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, true)
-                          : attn_kernel_for<1>(head_dim, group, caote, true);
-    if (!fs || !fc) return hipErrorInvalidDeviceFunction;
+    void *fs = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, false, p.splits)
+                          : attn_kernel_for<1>(head_dim, group, caote, false, p.splits);
+    void *fc = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, true, p.splits)
+                          : attn_kernel_for<1>(head_dim, group, caote, true, p.splits);
+    if (!fs || !fc || p.splits > kMaxSplits) return hipErrorInvalidDeviceFunction;
     void *args[] = {const_cast<UnitParams *>(&p)};
     const unsigned sz = (unsigned)(num_seqs * p.num_layers);
     hipError_t e = hipLaunchKernel(fs, dim3(p.splits, p.num_kv_heads, sz), dim3(kAttnThreads), args,
                                    split_lds, stream);
     if (e != hipSuccess) return e;
-    return hipLaunchKernel(fc, dim3(p.num_kv_heads, sz), dim3(kAttnThreads), args, 0, stream);
+    const bool few = !caote && p.splits <= kMergeBatch;
+    return hipLaunchKernel(fc, dim3(p.num_kv_heads, sz), dim3(few ? kAttnThreads : kCombineThreads), args, 0, stream);
 }
 
 hipError_t scratch_memory(hipStream_t stream, void **ptr) {

@@ -70,7 +70,7 @@ struct UnitParams {
     float *ws_acc;            // [U][splits][G][D] partial outputs (unnormalised)
     float *ws_ml;             // [U][splits][G][2] partial max logit (log2 units) and weight sum
     unsigned long long *ws_amin;  // [U][splits] (key << 32 | ~slot) of the lowest score
-    float *ws_rows;           // FastCAOTE: [U][capacity][G + 1] log2 logits of the G heads, distance
+    float *ws_rows;           // FastCAOTE: [U][G + 1][capacity] log2 logits of the G heads, distances
     int32_t splits, split_rows;   // row splits per unit and rows per split
     float qscale;             // softmax scale times log2(e)
     int32_t pad1;
