@@ -336,6 +336,13 @@ template <int O> __device__ __forceinline__ double xor_sum(double x) {
     }
 }
 
+template <int O> __device__ __forceinline__ float pair_sum(float x) {
+    const unsigned b = __float_as_uint(x);
+    const auto r = O == 16 ? __builtin_amdgcn_permlane16_swap(b, b, false, false)
+                           : __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Column sums of per-lane fp64 partials (each lane holds EPL columns of its
 // chunk), in a fixed order: thread t < D receives the total of column t (no
 // other thread receives anything).  `red` holds NW*D doubles; the caller
@@ -1760,7 +1767,7 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
     }
     unsigned long long amin = ~0ull;
 
-    // Rows of 16 lanes (bf16 with d = 128, fp32 with d = 64): the tile's
+    // Rows of 16 lanes or more (all but bf16 with d = 64): the tile's
     // 2 * (G + 1) row sums (G logits and a distance per row) are reduced
     // together, each exchange leaving every lane with half as many values:
     // the row's lower half keeps row 0 and its upper half row 1 (row_mirror),
@@ -1769,8 +1776,10 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
     // holds row k / 2: head k % 2 (and, with G = 4, head 2 + k % 2) and the
     // distance.  Each bank takes its weights' exponentials once, and every
     // lane receives all of them by row_newbcast from the first lane of each
-    // bank.
-    constexpr bool kPacked = LPR == 16 && kAttnRows == 2;
+    // bank.  A row of 32 or 64 lanes spans two or four such lane rows, whose
+    // sums are added at the end (three or two values per lane); each then goes
+    // on with the same values.
+    constexpr bool kPacked = LPR >= 16 && kAttnRows == 2;
     constexpr int NQ = G == 4 ? 2 : 1;  // logits per lane after the reduction
     // With G = 4 the weighted sum of the value rows runs on the matrix cores:
     // v_mfma_f32_4x4x1_16b_f32 treats each quad of lanes as a block whose
@@ -1852,6 +1861,16 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
         }
         pd += dpp<0x4E>(pd);
         pd += dpp<0xB1>(pd);
+        if constexpr (LPR >= 32) {
+#pragma unroll
+            for (int h = 0; h < NQ; ++h) q[h] = pair_sum<16>(q[h]);
+            pd = pair_sum<16>(pd);
+        }
+        if constexpr (LPR >= 64) {
+#pragma unroll
+            for (int h = 0; h < NQ; ++h) q[h] = pair_sum<32>(q[h]);
+            pd = pair_sum<32>(pd);
+        }
         // this lane's logits: head hq[h] of row rb
         const int e = e0 + rb * GROUPS + grp;
         const bool vr = e < r1;
