@@ -1681,27 +1681,33 @@ template <int DT, int D> struct AttnShape {
 };
 
 // fp64 mean of a unit's n rows from the running sum (count rows) plus the rows
-// [count, n) read here, as a pair of fp32 numbers: its rounding into
-// mean[0 .. D) and the rest into mean_lo[0 .. D); thread t < D takes column t.
-template <int DT, int D>
-__device__ __forceinline__ void attn_mean(const double *st, const char *vb, uint32_t ss, int n,
-                                          int count, float *mean, float *mean_lo) {
-    if (threadIdx.x < D) {
-        const int t = threadIdx.x;
-        double f = 0.0;
-        for (int r = count; r < n; ++r) f += (double)row_elem<DT>(vb + (size_t)r * ss, t);
-        const double old = count > 0 ? st[t] : 0.0;
-        const double m = (old + f) / (double)n;
-        const float hi = (float)m;
-        mean[t] = hi;
-        mean_lo[t] = (float)(m - (double)hi);
+// [count, n), as a pair of fp32 numbers: its rounding into mean[0 .. D) and the
+// rest into mean_lo[0 .. D); thread t < D takes column t.  The sum, its count
+// and the newest row, which the state usually lacks alone, are loaded at once
+// (MeanLoads); any other rows are read when the count is known.
+template <int DT, int D> struct MeanLoads {
+    double cnt, old;
+    float newest;
+    __device__ __forceinline__ void load(const double *st, const char *vb, uint32_t ss, int n) {
+        const int t = min((int)threadIdx.x, D - 1);
+        cnt = st[D];
+        old = st[t];
+        newest = row_elem<DT>(vb + (size_t)max(n - 1, 0) * ss, t);
     }
-}
-
-__device__ __forceinline__ int state_count(const double *st, int n) {
-    const double c = st[0];
-    return (c >= 0.0 && c <= (double)n && c == (double)(int)c) ? (int)c : 0;
-}
+    __device__ __forceinline__ void finish(const char *vb, uint32_t ss, int n, float *mean, float *mean_lo) const {
+        const int count = (cnt >= 0.0 && cnt <= (double)n && cnt == (double)(int)cnt) ? (int)cnt : 0;
+        if (threadIdx.x < D) {
+            const int t = threadIdx.x;
+            double f = 0.0;
+            for (int r = count; r < n - 1; ++r) f += (double)row_elem<DT>(vb + (size_t)r * ss, t);
+            if (count < n) f += (double)newest;
+            const double m = ((count > 0 ? old : 0.0) + f) / (double)n;
+            const float hi = (float)m;
+            mean[t] = hi;
+            mean_lo[t] = (float)(m - (double)hi);
+        }
+    }
+};
 
 // CAOTE: the FastCAOTE variant (App. A, Eq. app_fastcaote), whose score needs
 // every row's weight under the merged softmax: each row's G logits (log2
@@ -1741,14 +1747,34 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
     const int r1 = min(n, r0 + p.split_rows);
     const int64_t wsi = u * p.splits + sp;
 
-    if (r1 > r0) attn_mean<DT, D>(st, vb, ss32, n, state_count(st + D, n), mean, mean_lo);
+    // Everything the first tile needs is requested at once, so that the block
+    // waits for memory once before its row loop: the mean's inputs, the query
+    // rows and the first tile.
+    MeanLoads<DT, D> ml;
+    ml.load(st, vb, ss32, n);
     // this lane's columns of the G query rows, pre-scaled
     float qs[G][EPL];
     const float *qrow = p.q + (((int64_t)sl * p.num_layers + layer) * p.num_kv_heads + head) * G * D;
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) qs[g][i] = qrow[g * D + cl * EPL + i] * p.qscale;
+        for (int i = 0; i < EPL; ++i) qs[g][i] = qrow[g * D + cl * EPL + i];
+    __builtin_amdgcn_sched_barrier(0);
+    // chunk j of a tile: row j/2 of this group's kAttnRows rows, K for even j, V for odd
+    uint4 buf[2 * kAttnRows];
+    auto chunk_off = [&](int e0, int j, uint32_t z) __attribute__((always_inline)) {
+        return row_off(max(min(e0 + (j >> 1) * GROUPS + grp, r1 - 1), 0), ss32, cl) + z;
+    };
+#pragma unroll
+    for (int j = 0; j < 2 * kAttnRows; ++j) {  // (a split past the end reads row 0, unused)
+        buf[j] = load_stream((j & 1) ? vb : kb, chunk_off(r0, j, 0u));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (r1 > r0) ml.finish(vb, ss32, n, mean, mean_lo);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) qs[g][i] *= p.qscale;
     __syncthreads();
     float mv[EPL], mvl[EPL];
 #pragma unroll
@@ -1989,16 +2015,6 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
     };
 
     if (r1 > r0) {
-        // chunk j of a tile: row j/2 of this group's kAttnRows rows, K for even j, V for odd
-        uint4 buf[2 * kAttnRows];
-        auto chunk_off = [&](int e0, int j, uint32_t z) __attribute__((always_inline)) {
-            return row_off(min(e0 + (j >> 1) * GROUPS + grp, r1 - 1), ss32, cl) + z;
-        };
-#pragma unroll
-        for (int j = 0; j < 2 * kAttnRows; ++j) {
-            buf[j] = load_stream((j & 1) ? vb : kb, chunk_off(r0, j, 0u));
-            __builtin_amdgcn_sched_barrier(0);
-        }
         if constexpr (kPacked) {
             for (int e0 = r0; e0 < r1; e0 += A::TILE) packed_tile(e0, buf);
         }
@@ -2139,11 +2155,12 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
         p.ws_amin[wsi] = m;
     }
     if constexpr (CAOTE) {  // the rows' logits and distances (written before the barrier above)
+        const int rows_here = max(r1 - r0, 0);
         float *dst = p.ws_rows + u * p.capacity * (G + 1) + r0;
-#pragma unroll
-        for (int g = 0; g <= G; ++g)
-            for (int i = threadIdx.x; i < r1 - r0; i += kAttnThreads)
-                dst[g * p.capacity + i] = rows[lds_ix<kSiteRows>(g * p.split_rows + i, p.split_rows * (G + 1))];
+        for (int i = threadIdx.x; i < rows_here * (G + 1); i += kAttnThreads) {
+            const int g = i / rows_here, r = i - g * rows_here;
+            dst[g * p.capacity + r] = rows[lds_ix<kSiteRows>(g * p.split_rows + r, p.split_rows * (G + 1))];
+        }
     }
 }
 
