@@ -294,6 +294,23 @@ vd_status vd_decode_attention_evict_noalloc(const vd_cache_desc *desc, const flo
 /* Bytes of the static device array behind vd_decode_attention_evict_noalloc. */
 size_t vd_decode_attention_noalloc_max_bytes(void);
 
+/* vd_evict_step with device scratch, through which several workgroups share the
+ * rows of each unit where the cache has at most half as many units as the GPU
+ * has compute units.  Arguments, results and errors are vd_evict_step's, and:
+ *
+ *   scratch      device, 16-byte aligned, at least vd_evict_step_split_size()
+ *                bytes (may be NULL when that is 0), of any content; calls that
+ *                share a scratch must not overlap
+ *
+ * VD_ERR_WORKSPACE for a missing, misaligned or short scratch. */
+vd_status vd_evict_step_split(const vd_cache_desc *desc, const int32_t *n_valid, const int32_t *budget,
+                              vd_variant variant, double *running_sum, int32_t *pos, float *scores_out,
+                              uint8_t *keep_out, void *scratch, size_t scratch_bytes, vd_stream stream);
+
+/* Bytes of scratch vd_evict_step_split needs for this descriptor: 0 where it
+ * does what vd_evict_step does (many units, or short ones). */
+size_t vd_evict_step_split_size(const vd_cache_desc *desc);
+
 /* Bytes of device workspace vd_evict_step needs for this descriptor (0 in this build). */
 size_t vd_evict_step_workspace_size(const vd_cache_desc *desc);
 

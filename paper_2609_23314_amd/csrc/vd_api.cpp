@@ -236,6 +236,94 @@ vd_status plan_step(const vd_cache_desc *d, UnitParams &p, int ns, bool score_mo
     return plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kBlock, vd::kLdsBytes, false, lds_bytes);
 }
 
+// Splits of a pass over `units` units of at most n rows: the workgroups that the
+// units leave idle CUs for, each with at least kSplitBytes of rows (what one
+// tile of a workgroup's stream holds is twice that).  The second launch costs
+// about 5 us of the GPU's time (its start, the keys' way through memory) and 3 us
+// of the host's, which units below kSplitUnitBytes do not win back.  Measured, one
+// workgroup and split, us: 32 units of 2049 x 128 B 13.4 and 15.1, 1280 x 256 B
+// 17.4 and 20.1, 2560 x 256 B 24.6 and 22.7 (with its append 29.0 and 28.4, and the
+// host the slower of the two), 4096 x 256 B 32.2 and 23.8, 8193 x 256 B 45.8 and
+// 19.7; two splits of 128 units, 4096 x 256 B 40.5 and 39.6, 8193 x 256 B 58.3 and
+// 52.9.
+constexpr int64_t kSplitBytes = 64 * 1024, kSplitUnitBytes = 768 * 1024;
+int max_splits(int64_t units) { return units > 0 ? int(std::min<int64_t>(64, vd::kCus / units)) : 0; }
+int step_splits(int64_t units, int64_t n, int64_t row_bytes) {
+    return n * row_bytes < kSplitUnitBytes ? 0 : int(std::min<int64_t>(max_splits(units), n * row_bytes / kSplitBytes));
+}
+// Scratch of a split pass: the keys, the column sums, the sums' partials.
+struct SplitWs {
+    int64_t keys_stride, tot, part, total;  // keys per unit, byte offsets, bytes in all
+};
+SplitWs split_ws_layout(const vd_cache_desc *d, int64_t units) {
+    SplitWs w;
+    w.keys_stride = (int64_t(d->capacity) + 3) / 4 * 4;
+    w.tot = align16(units * w.keys_stride * 4);
+    w.part = w.tot + units * d->head_dim * 8;
+    w.total = w.part + units * max_splits(units) * d->head_dim * 8;
+    return w;
+}
+int64_t step_units(const vd_cache_desc *d) { return int64_t(d->num_seqs) * d->num_layers * d->num_kv_heads; }
+
+// The pass over a validated call; scratch (or null): split_ws_layout's bytes.
+vd_status evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const int32_t *budget,
+                     vd_variant variant, double *running_sum, int32_t *pos, float *scores_out,
+                     uint8_t *keep_out, char *scratch, hipStream_t stream) {
+    vd_status st;
+    for (int s0 = 0; s0 < desc->num_seqs; s0 += vd::kMaxSeqsPerLaunch) {
+        const int ns = std::min(vd::kMaxSeqsPerLaunch, desc->num_seqs - s0);
+        UnitParams p = base_params(desc, s0, ns, n_valid, budget);
+        hand_scored_rows(p, variant);
+        p.mode = vd::kModeStep;
+        p.running_sum = running_sum;
+        p.pos = pos;
+        p.scores = scores_out;
+        p.keep = keep_out;
+        int splits = 0;
+        if (scratch) {
+            int nmax = 0;  // rows of the longest unit that evicts
+            for (int i = 0; i < ns; ++i)
+                if (p.nN[2 * i] > p.nN[2 * i + 1]) nmax = std::max(nmax, p.nN[2 * i]);
+            splits = step_splits(step_units(desc), nmax, int64_t(desc->head_dim) * elem_bytes(desc->dtype));
+        }
+        size_t lds = 0;
+        if (splits > 1) {  // at most half as many units as CUs, so one launch holds them all
+            const SplitWs ws = split_ws_layout(desc, step_units(desc));
+            p.splits = splits;
+            p.units = int32_t(step_units(desc));
+            p.ws_keys = reinterpret_cast<uint32_t *>(scratch);
+            p.ws_tot = reinterpret_cast<double *>(scratch + ws.tot);
+            p.ws_part = reinterpret_cast<double *>(scratch + ws.part);
+            p.keys_stride = ws.keys_stride;
+            if ((st = plan_step_lds(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, vd::kBlock,
+                                    vd::kLdsBytes, false, lds)) != VD_OK)
+                return st;
+            st = launched(vd::launch_split_step(p, ns, desc->dtype, desc->head_dim, variant, lds, stream));
+        } else {
+            if ((st = plan_step(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, lds)) != VD_OK)
+                return st;
+            st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds, stream));
+        }
+        if (st != VD_OK) return st;
+    }
+    return VD_OK;
+}
+
+vd_status check_evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const int32_t *budget,
+                           vd_variant variant, const double *running_sum, const int32_t *pos,
+                           const float *scores_out) {
+    vd_status st = check_desc(desc);
+    if (st != VD_OK) return st;
+    if (!budget) return VD_ERR_INVALID_ARG;
+    if ((st = check_counts(desc, n_valid, budget)) != VD_OK) return st;
+    if (!pass_variant(variant)) return VD_ERR_INVALID_ARG;
+    if (key_side(variant) && !desc->k) return VD_ERR_INVALID_ARG;
+    if ((running_sum && !aligned(running_sum, 8)) || (pos && !aligned(pos, 4)) ||
+        (scores_out && !aligned(scores_out, 4)))
+        return VD_ERR_INVALID_ARG;
+    return VD_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -329,32 +417,29 @@ vd_status vd_evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const
                         vd_stream stream) {
     (void)workspace;
     (void)workspace_bytes;
-    vd_status st = check_desc(desc);
+    const vd_status st = check_evict_step(desc, n_valid, budget, variant, running_sum, pos, scores_out);
     if (st != VD_OK) return st;
-    if (!budget) return VD_ERR_INVALID_ARG;
-    if ((st = check_counts(desc, n_valid, budget)) != VD_OK) return st;
-    if (!pass_variant(variant)) return VD_ERR_INVALID_ARG;
-    if (key_side(variant) && !desc->k) return VD_ERR_INVALID_ARG;
-    if ((running_sum && !aligned(running_sum, 8)) || (pos && !aligned(pos, 4)) ||
-        (scores_out && !aligned(scores_out, 4)))
-        return VD_ERR_INVALID_ARG;
-    for (int s0 = 0; s0 < desc->num_seqs; s0 += vd::kMaxSeqsPerLaunch) {
-        const int ns = std::min(vd::kMaxSeqsPerLaunch, desc->num_seqs - s0);
-        UnitParams p = base_params(desc, s0, ns, n_valid, budget);
-        hand_scored_rows(p, variant);
-        p.mode = vd::kModeStep;
-        p.running_sum = running_sum;
-        p.pos = pos;
-        p.scores = scores_out;
-        p.keep = keep_out;
-        size_t lds = 0;
-        if ((st = plan_step(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, lds)) != VD_OK)
-            return st;
-        st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds,
-                                      reinterpret_cast<hipStream_t>(stream)));
-        if (st != VD_OK) return st;
-    }
-    return VD_OK;
+    return evict_step(desc, n_valid, budget, variant, running_sum, pos, scores_out, keep_out, nullptr,
+                      reinterpret_cast<hipStream_t>(stream));
+}
+
+vd_status vd_evict_step_split(const vd_cache_desc *desc, const int32_t *n_valid, const int32_t *budget,
+                              vd_variant variant, double *running_sum, int32_t *pos, float *scores_out,
+                              uint8_t *keep_out, void *scratch, size_t scratch_bytes, vd_stream stream) {
+    const vd_status st = check_evict_step(desc, n_valid, budget, variant, running_sum, pos, scores_out);
+    if (st != VD_OK) return st;
+    const size_t need = vd_evict_step_split_size(desc);
+    if (need && (!scratch || !aligned(scratch, 16) || scratch_bytes < need)) return VD_ERR_WORKSPACE;
+    return evict_step(desc, n_valid, budget, variant, running_sum, pos, scores_out, keep_out,
+                      need ? static_cast<char *>(scratch) : nullptr, reinterpret_cast<hipStream_t>(stream));
+}
+
+size_t vd_evict_step_split_size(const vd_cache_desc *desc) {
+    if (check_desc(desc) != VD_OK) return 0;
+    const int64_t units = step_units(desc);
+    const int64_t row_bytes = int64_t(desc->head_dim) * elem_bytes(desc->dtype);
+    if (step_splits(units, desc->capacity, row_bytes) < 2) return 0;
+    return size_t(split_ws_layout(desc, units).total);
 }
 
 vd_status vd_geometry(const vd_cache_desc *desc, const int32_t *n_valid, const double *k_sum,

@@ -667,7 +667,20 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
 
 // ---------------------------------------------------------------- the pass
 
-template <int DT, int D, int VAR, int THREADS>
+// Parts of the pass: all of it in one workgroup per unit, or, where a launch
+// has at most half as many units as the chip has CUs, the rows' scores by
+// p.splits workgroups per unit (kRows) and then the rest by one (kFinish).  A
+// single CU streams about 60 GB/s, so a launch of few units leaves the memory
+// idle: kRows spreads each unit's rows over the idle CUs.  Every kRows workgroup
+// of a unit sums the unit's new rows itself (the same sums in the same order as
+// the whole pass; those few rows come from L2 after the first workgroup) and
+// scores its share of the rest; the keys go through p.ws_keys.  Without a running
+// sum, sum_kernel's partials stand in for a state that covers every row.
+// One GPU, bf16, one workgroup -> split, us: 32 units, d = 128, n = 8193, N = 8192
+// 45.8 -> 19.7 (one unit 40.4 -> 14.9); 36 units, d = 256, n = 5120, N = 4096 73.7 ->
+// 43.6; 32 units, d = 128, n = 8192 without a running sum 154 -> 93.
+enum : int { kWhole = 0, kRows = 1, kFinish = 2 };
+template <int DT, int D, int VAR, int THREADS, int PART = kWhole>
 __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
     using S = Shape<DT, D, THREADS>;
     constexpr int NT = THREADS, NW = NT / 64;
@@ -682,7 +695,18 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
     const int keys_words = (p.off_lists - p.off_keys) / 4;  // the keys region (keys, hist2; red)
     const int red_cap = (p.off_lists - p.off_keys) / 8;
 
-    const int head = blockIdx.x, layer = blockIdx.y, sl = blockIdx.z;
+    int head = blockIdx.x, layer = blockIdx.y, sl = blockIdx.z, split = 0;
+    if constexpr (PART == kRows) {
+        // split-major: with a multiple of eight units all splits of a unit run on
+        // one XCD and share its L2 for the unit's new rows
+        int x = blockIdx.x;
+        split = x / p.units;
+        x -= split * p.units;
+        head = x % p.num_kv_heads;
+        x /= p.num_kv_heads;
+        layer = x % p.num_layers;
+        sl = x / p.num_layers;
+    }
     const int ul = (sl * p.num_layers + layer) * p.num_kv_heads + head;
     const int64_t u = (int64_t)p.unit0 + ul;
     const int n = p.nN[2 * sl], N = p.nN[2 * sl + 1];
@@ -723,7 +747,19 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
     // arrive in one batch and the row tiles go out right behind them.
     const double *stp = st ? st : reinterpret_cast<const double *>(vb);
     const double craw = stp[st ? D : 0];
-    const double st_col = stp[st ? min((int)threadIdx.x, D) : 0];
+    double st_col = stp[st ? min((int)threadIdx.x, D) : 0];
+    if constexpr (PART == kRows) {
+        if (!st) {  // sum_kernel's column sums of all n rows
+            const double *part = p.ws_part + u * p.splits * D + min((int)threadIdx.x, D - 1);
+            st_col = 0.0;
+#pragma unroll 8
+            for (int i = 0; i < p.splits; ++i) st_col += part[i * D];
+        }
+    }
+    // what the state covers: the caller's rows but the new ones, or (kRows
+    // without a running sum) all of them
+    const bool sums = PART == kRows || st;
+    const int expect = PART == kRows && !st ? n : min(N, n);
     const int lastrow = max(n - 1, 0);
     constexpr int kStep = S::GROUPS * kChunks;  // rows per tile of the stream
     // A first part of at most one row per lane group (a decode step appends
@@ -734,6 +770,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
     // first part: element e of it is row e below cnt and row e + staged above.
     struct Plan {
         int cnt, fresh, staged, tiles_f, second, tiles;  // second: rows of the scoring part
+        int at;                                          // kRows: its first element
         bool small;                                      // first part in one chunk, staged
     };
     auto plan_for = [&](int cnt) __attribute__((always_inline)) {
@@ -744,10 +781,19 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
         q.small = q.fresh > 0 && q.fresh <= S::GROUPS && q.fresh <= arg_stash;
         q.tiles_f = q.small ? 0 : (q.fresh + kStep - 1) / kStep;
         q.second = !need_scores ? 0 : n - q.staged;
+        q.at = 0;
+        if constexpr (PART == kRows) {  // this workgroup's share, in whole row groups
+            const int per = ((q.second + p.splits - 1) / p.splits + S::GROUPS - 1) / S::GROUPS * S::GROUPS;
+            q.at = min(split * per, q.second);
+            q.second = min(per, q.second - q.at);
+        }
         q.tiles = q.tiles_f + (q.second + kStep - 1) / kStep;
         return q;
     };
-    auto srow = [&](const Plan &q, int e) __attribute__((always_inline)) { return e < q.cnt ? e : e + q.staged; };
+    auto srow = [&](const Plan &q, int e) __attribute__((always_inline)) {
+        if constexpr (PART == kRows) e += q.at;
+        return e < q.cnt ? e : e + q.staged;
+    };
     // chunk k of tile t of the stream; a tile past the end reads the last row
     // (never used)
     auto load_chunk = [&](const Plan &q, int t, int k, uint32_t z = 0u) __attribute__((always_inline)) -> uint4 {
@@ -767,31 +813,35 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
     auto load_small = [&](const Plan &q) __attribute__((always_inline)) -> uint4 {
         return load_stream(vb, row_off(min(q.cnt + eb, lastrow), ss32, cl));
     };
-    const Plan guessed = plan_for(st ? min(N, n) : 0);
+    const Plan guessed = plan_for(sums ? expect : 0);
     uint4 buf[kChunks], fc;
-    if (guessed.small) fc = load_small(guessed);
-    load_v(guessed, 0, buf);
+    if constexpr (PART != kFinish) {
+        if (guessed.small) fc = load_small(guessed);
+        load_v(guessed, 0, buf);
+    }
 
     if (n <= 0) {
-        if (st) {
+        if (st && PART != kRows) {
             for (int t = threadIdx.x; t <= D; t += NT) st[t] = 0.0;
         }
         return;
     }
     if (!need_scores && !st) {
-        for (int j = threadIdx.x; keep_out && j < n; j += NT) keep_out[j] = 1;
+        for (int j = threadIdx.x; PART != kRows && keep_out && j < n; j += NT) keep_out[j] = 1;
         return;
     }
-    int count = 0;
+    int count = PART == kRows && !st ? n : 0;
     if (st) count = (craw >= 0.0 && craw <= (double)n && craw == (double)(int)craw) ? (int)craw : 0;
     const Plan q = count == guessed.cnt ? guessed : plan_for(count);
-    if (count != guessed.cnt) {
-        if (q.small) fc = load_small(q);
-        load_v(q, 0, buf);
+    if constexpr (PART != kFinish) {
+        if (count != guessed.cnt) {
+            if (q.small) fc = load_small(q);
+            load_v(q, 0, buf);
+        }
     }
     const int fresh = q.fresh;
-    const int staged = q.staged;             // first-part rows in LDS
-    const bool stashed = staged == fresh;    // all of them
+    const int staged = PART == kFinish ? 0 : q.staged;  // first-part rows in LDS
+    const bool stashed = PART != kFinish && staged == fresh;  // all of them
     auto sfetch = [&](int r, int c) __attribute__((always_inline)) -> uint4 {
         return *reinterpret_cast<const uint4 *>(stash + (int64_t)lds_ix<kSiteStash>(r - count, p.stash_rows) * S::ROWB +
                                                 c * 16);
@@ -926,7 +976,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
         if (cl < 4 && e < lim) {
             const uint32_t key = key_of<VAR>(s);
             if (to_lds) {
-                keys[lds_ix<kSiteKeys>(rbase + e + (e >= gap_at ? gap : 0), p.keys_cap)] = key;
+                keys[lds_ix<kSiteKeys>(rbase + e + (rbase + e >= gap_at ? gap : 0), p.keys_cap)] = key;
                 kmin = min(kmin, key);
                 kmax = max(kmax, key);
             }
@@ -942,7 +992,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
             float a[4];
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) a[k] = partial(w4[k]);
-            score4(a, e0, staged, count, staged, 0);
+            score4(a, e0, staged, count, 0, 0);
         } else {
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) {
@@ -999,7 +1049,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-                score4(a, e0 + h * NW * S::RPW, q.second, 0, q.cnt, q.staged);
+                score4(a, e0 + h * NW * S::RPW, q.second, PART == kRows ? q.at : 0, q.cnt, q.staged);
             }
         } else {
 #pragma unroll
@@ -1013,20 +1063,64 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
             }
         }
     };
-    {
+    if constexpr (PART == kFinish) {
+        if (st && threadIdx.x < D) {
+            H.old_sum[threadIdx.x] = count > 0 ? st_col : 0.0;
+            H.sum[threadIdx.x] = p.ws_tot[u * D + threadIdx.x];
+        }
+        if (to_lds) {  // the keys (a unit's lie on a 16-byte boundary; the host admits 16384 at most)
+            const uint4 *src = reinterpret_cast<const uint4 *>(p.ws_keys + u * p.keys_stride);
+            constexpr int kWords = (kMaxSplitSlots / 4 + NT - 1) / NT;
+            uint4 w[kWords];
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) w[i] = src[min((int)threadIdx.x + i * NT, (n - 1) / 4)];
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) {
+                const int j = 4 * (threadIdx.x + i * NT);
+                const uint32_t k[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (j + c >= n) continue;
+                    keys[lds_ix<kSiteKeys>(j + c, p.keys_cap)] = k[c];
+                    kmin = min(kmin, k[c]);
+                    kmax = max(kmax, k[c]);
+                }
+            }
+        }
+    } else {
         const int T = q.tiles;
         int t = 0;
         if (q.small) mean_body(eb, eb < fresh, fc);
         for (; t < q.tiles_f && t + 1 < T; ++t) use_fresh(t, std::true_type{});
         if (t < q.tiles_f) use_fresh(t++, std::false_type{});  // no scoring part follows
         finish_mean();
-        int si = 0;  // staged tiles scored
+        constexpr bool kShare = PART == kRows;  // the splits take the staged tiles in turn
+        const int sstep = kShare ? p.splits : 1;
+        int si = kShare ? split : 0;  // staged tiles scored
         for (; t + 1 < T; ++t) {
             use_scored(t, std::true_type{});
-            if (si < stash_tiles) score_stash_tile(si++);
+            if (si < stash_tiles) {
+                score_stash_tile(si);
+                si += sstep;
+            }
         }
-        for (; si < stash_tiles; ++si) score_stash_tile(si);
+        for (; si < stash_tiles; si += sstep) score_stash_tile(si);
         if (t < T) use_scored(t, std::false_type{});  // the last tile: no load past the end
+    }
+    if constexpr (PART == kRows) {  // the keys of this workgroup's rows, and the unit's column sums
+        __syncthreads();
+        if (to_lds) {
+            uint32_t *out = p.ws_keys + u * p.keys_stride;
+            for (int e = threadIdx.x; e < q.second; e += NT) {
+                const int j = srow(q, e);
+                out[j] = keys[lds_ix<kSiteKeys>(j, p.keys_cap)];
+            }
+            for (int i = split; i < stash_tiles; i += p.splits)
+                for (int e = i * S::STEP + threadIdx.x; e < min(staged, (i + 1) * S::STEP); e += NT)
+                    out[count + e] = keys[lds_ix<kSiteKeys>(count + e, p.keys_cap)];
+        }
+        if (st && split == 0 && threadIdx.x < D) p.ws_tot[u * D + threadIdx.x] = H.sum[threadIdx.x];
+        return;
     }
     if (to_lds) {  // what the selection reads after the barrier below
         kmin = wave_min_u32(kmin);
@@ -1243,6 +1337,45 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
         for (int t = threadIdx.x; t < D; t += NT) st[t] = H.sum[t];
         if (threadIdx.x == 0) st[D] = (double)n;
     }
+}
+
+// Column sums of a unit's n rows in p.splits parts (p.ws_part: [unit][split][D]),
+// for a split pass without a running sum.  Bound by HBM, like the rows' scores.
+template <int DT, int D> __global__ void __launch_bounds__(NT) sum_kernel(const UnitParams p) {
+    using S = Shape<DT, D>;
+    extern __shared__ __align__(16) unsigned char lds[];
+    double *red = reinterpret_cast<double *>(lds);
+    int x = blockIdx.x;
+    const int split = x / p.units, ul = x - split * p.units;  // (split-major, as the rows' scores)
+    x = ul;
+    const int head = x % p.num_kv_heads;
+    x /= p.num_kv_heads;
+    const int layer = x % p.num_layers, sl = x / p.num_layers;
+    const int64_t u = (int64_t)p.unit0 + ul;
+    const int n = p.nN[2 * sl];
+    const char *vb = p.v + (int64_t)sl * p.s_seq + (int64_t)layer * p.s_layer + (int64_t)head * p.s_head;
+    const int per = (n + p.splits - 1) / p.splits;
+    const int r0 = min(split * per, n), r1 = min(r0 + per, n);
+    const int lane = lane_id(), cl = lane % S::LPR, g = wave_id() * S::RPW + lane / S::LPR;
+    double acc[S::EPL];
+#pragma unroll
+    for (int i = 0; i < S::EPL; ++i) acc[i] = 0.0;
+    for (int r = r0; r < r1; r += S::GROUPS * kChunks) {
+        uint4 w[kChunks];
+#pragma unroll
+        for (int k = 0; k < kChunks; ++k)  // (cacheable: the rows are read again for their scores)
+            w[k] = *reinterpret_cast<const uint4 *>(vb + row_off(min(r + k * S::GROUPS + g, r1 - 1), p.s_slot, cl));
+#pragma unroll
+        for (int k = 0; k < kChunks; ++k) {
+            if (r + k * S::GROUPS + g >= r1) continue;
+            float v[S::EPL];
+            Elem<DT>::unpack(w[k], v);
+#pragma unroll
+            for (int i = 0; i < S::EPL; ++i) acc[i] += (double)v[i];
+        }
+    }
+    const double s = block_col_total<DT, D>(acc, red, NW * D);
+    if (threadIdx.x < D) p.ws_part[(u * p.splits + split) * D + threadIdx.x] = s;
 }
 
 // Standalone selection: scores (global) -> keep mask.
@@ -2506,21 +2639,36 @@ template <int DT> void *attn_kernel_for(int head_dim, int group, bool caote, boo
 
 // The ABI's variants onto the kernel's score forms (a key-side variant is the
 // value-side form on the rows the host passes in V's place).
-template <int DT, int D, int THREADS> void *step_kernel_for(int variant) {
+template <int DT, int D, int THREADS, int PART> void *step_kernel_for(int variant) {
     switch (variant) {
-        case 0: case 3: return reinterpret_cast<void *>(&step_kernel<DT, D, kL2, THREADS>);
-        case 1: case 4: return reinterpret_cast<void *>(&step_kernel<DT, D, kDir, THREADS>);
-        case 2: return reinterpret_cast<void *>(&step_kernel<DT, D, kNorm, THREADS>);
-        case 5: return reinterpret_cast<void *>(&step_kernel<DT, D, kKeepSmallest, THREADS>);
+        case 0: case 3: return reinterpret_cast<void *>(&step_kernel<DT, D, kL2, THREADS, PART>);
+        case 1: case 4: return reinterpret_cast<void *>(&step_kernel<DT, D, kDir, THREADS, PART>);
+        case 2: return reinterpret_cast<void *>(&step_kernel<DT, D, kNorm, THREADS, PART>);
+        case 5: return reinterpret_cast<void *>(&step_kernel<DT, D, kKeepSmallest, THREADS, PART>);
     }
     return nullptr;
 }
 
-template <int DT, int THREADS> void *step_kernel_for(int head_dim, int variant) {
+template <int DT, int THREADS, int PART> void *step_kernel_for(int head_dim, int variant) {
+    // (the finishing part depends on the variant by its keys' order alone)
+    if (PART == kFinish) variant = variant == 5 ? 5 : 2;
     switch (head_dim) {
-        case 64: return step_kernel_for<DT, 64, THREADS>(variant);
-        case 128: return step_kernel_for<DT, 128, THREADS>(variant);
-        case 256: return step_kernel_for<DT, 256, THREADS>(variant);
+        case 64: return step_kernel_for<DT, 64, THREADS, PART>(variant);
+        case 128: return step_kernel_for<DT, 128, THREADS, PART>(variant);
+        case 256: return step_kernel_for<DT, 256, THREADS, PART>(variant);
+    }
+    return nullptr;
+}
+template <int THREADS, int PART> void *step_kernel_for(int dtype, int head_dim, int variant) {
+    return dtype == 0 ? step_kernel_for<0, THREADS, PART>(head_dim, variant)
+                      : step_kernel_for<1, THREADS, PART>(head_dim, variant);
+}
+
+template <int DT> void *sum_kernel_for(int head_dim) {
+    switch (head_dim) {
+        case 64: return reinterpret_cast<void *>(&sum_kernel<DT, 64>);
+        case 128: return reinterpret_cast<void *>(&sum_kernel<DT, 128>);
+        case 256: return reinterpret_cast<void *>(&sum_kernel<DT, 256>);
     }
     return nullptr;
 }
@@ -2546,11 +2694,24 @@ hipError_t launch(void *fn, int num_seqs, size_t lds_bytes, hipStream_t stream,
 
 hipError_t launch_step(const UnitParams &p, int num_seqs, int dtype, int head_dim,
                        int variant, size_t lds_bytes, hipStream_t stream) {
-    void *fn = p.threads == kHalfBlock ? (dtype == 0 ? step_kernel_for<0, kHalfBlock>(head_dim, variant)
-                                                     : step_kernel_for<1, kHalfBlock>(head_dim, variant))
-                                       : (dtype == 0 ? step_kernel_for<0, kBlock>(head_dim, variant)
-                                                     : step_kernel_for<1, kBlock>(head_dim, variant));
+    void *fn = p.threads == kHalfBlock ? step_kernel_for<kHalfBlock, kWhole>(dtype, head_dim, variant)
+                                       : step_kernel_for<kBlock, kWhole>(dtype, head_dim, variant);
     return launch(fn, num_seqs, lds_bytes, stream, p, p.threads);
+}
+
+hipError_t launch_split_step(const UnitParams &p, int num_seqs, int dtype, int head_dim, int variant,
+                             size_t lds_bytes, hipStream_t stream) {
+    void *rows = step_kernel_for<kBlock, kRows>(dtype, head_dim, variant);
+    void *finish = step_kernel_for<kBlock, kFinish>(dtype, head_dim, variant);
+    void *sum = dtype == 0 ? sum_kernel_for<0>(head_dim) : sum_kernel_for<1>(head_dim);
+    if (!rows || !finish || !sum) return hipErrorInvalidDeviceFunction;
+    void *args[] = {const_cast<UnitParams *>(&p)};
+    const dim3 grid(unsigned(p.splits) * unsigned(p.units));
+    hipError_t e = hipSuccess;
+    if (!p.running_sum) e = hipLaunchKernel(sum, grid, dim3(NT), args, size_t(NW) * head_dim * 8, stream);
+    if (e == hipSuccess) e = hipLaunchKernel(rows, grid, dim3(NT), args, lds_bytes, stream);
+    if (e != hipSuccess) return e;
+    return launch(finish, num_seqs, size_t(p.off_stash), stream, p);
 }
 
 hipError_t launch_select(const UnitParams &p, int num_seqs, size_t lds_bytes,

@@ -13,6 +13,7 @@ constexpr int kHalfBlock = kBlock / 2;    // the pass with two workgroups per CU
 constexpr int kCus = 256;                 // compute units of an MI355X
 constexpr int kMaxSeqsPerLaunch = 256;    // per-sequence n and N travel as kernel arguments
 constexpr int kLdsBytes = 160 * 1024;     // LDS of one gfx950 workgroup
+constexpr int kMaxSplitSlots = 16384;     // slots per unit of a split pass, at most
 
 enum Mode : int32_t { kModeStep = 0, kModeScore = 1 };
 
@@ -73,13 +74,21 @@ struct UnitParams {
     float *ws_rows;           // FastCAOTE: [U][G + 1][capacity] log2 logits of the G heads, distances
     int32_t splits, split_rows;   // row splits per unit and rows per split
     float qscale;             // softmax scale times log2(e)
-    int32_t pad1;
+    int32_t units;            // units of the launch (split pass)
+    // split pass: its workspace
+    uint32_t *ws_keys;        // [U][keys_stride] the rows' keys
+    double *ws_tot;           // [U][D] column sums of all n rows (with a running sum)
+    double *ws_part;          // [U][splits][D] their partial sums (without one)
+    int64_t keys_stride;      // a multiple of 4
     int32_t nN[2 * kMaxSeqsPerLaunch];   // n and N of each sequence of the launch, interleaved
 };
 
 // Each launches one workgroup per unit of `num_seqs` sequences.
 hipError_t launch_step(const UnitParams &p, int num_seqs, int dtype, int head_dim,
                        int variant, size_t lds_bytes, hipStream_t stream);
+// The same by p.splits workgroups per unit, then one (p.threads is kBlock).
+hipError_t launch_split_step(const UnitParams &p, int num_seqs, int dtype, int head_dim, int variant,
+                             size_t lds_bytes, hipStream_t stream);
 hipError_t launch_select(const UnitParams &p, int num_seqs, size_t lds_bytes,
                          hipStream_t stream);
 hipError_t launch_compact(const UnitParams &p, int num_seqs, int dtype, int head_dim,

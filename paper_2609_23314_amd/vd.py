@@ -66,7 +66,10 @@ def load():
     lib.vd_select_topn.argtypes = [D, P, P, P, P, P]
     lib.vd_compact.argtypes = [D, P, P, P, P, P]
     lib.vd_evict_step.argtypes = [D, P, P, I32, P, P, P, P, P, SZ, P]
-    for f in ("vd_score", "vd_select_topn", "vd_compact", "vd_evict_step"):
+    lib.vd_evict_step_split.argtypes = lib.vd_evict_step.argtypes
+    lib.vd_evict_step_split_size.argtypes = [D]
+    lib.vd_evict_step_split_size.restype = ctypes.c_size_t
+    for f in ("vd_score", "vd_select_topn", "vd_compact", "vd_evict_step", "vd_evict_step_split"):
         getattr(lib, f).restype = ctypes.c_int
     lib.vd_evict_step_workspace_size.argtypes = [D]
     lib.vd_evict_step_workspace_size.restype = ctypes.c_size_t
@@ -200,10 +203,19 @@ def vd_evict_step_workspace_size(v, k=None):
     return int(load().vd_evict_step_workspace_size(ctypes.byref(desc)))
 
 
+def vd_evict_step_split_size(v, k=None):
+    """Bytes of scratch that ``vd_evict_step`` can use to split units; 0: none."""
+    desc = cache_desc(v, k)
+    return int(load().vd_evict_step_split_size(ctypes.byref(desc)))
+
+
 def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=None,
                   scores_out=None, keep_out=None, workspace=None, *, num_q_heads=None,
-                  stream=None):
-    """One eviction pass over every unit, in place (see ``vd_evict_step`` in vd.h)."""
+                  stream=None, scratch=None):
+    """One eviction pass over every unit, in place (see ``vd_evict_step`` in vd.h).
+    With ``scratch`` (a uint8 tensor of ``vd_evict_step_split_size`` bytes, not
+    shared by calls that overlap) a pass over few units spreads each of them
+    over several workgroups (``vd_evict_step_split`` in vd.h)."""
     U, C, Dh = _units(v), v.shape[3], v.shape[4]
     desc = cache_desc(v, k, num_q_heads)
     n_h = _host_i32(n_valid, v.shape[0], "n_valid")
@@ -216,6 +228,13 @@ def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=Non
         _need(scores_out, "scores_out", torch.float32, U * C, v.device)
     if keep_out is not None:
         _need(keep_out, "keep_out", torch.uint8, U * C, v.device)
+    if scratch is not None:
+        _need(scratch, "scratch", torch.uint8, 0, v.device)
+        _check("vd_evict_step_split", load().vd_evict_step_split(
+            ctypes.byref(desc), _ptr(n_h), _ptr(b_h), VARIANTS[variant], _ptr(running_sum),
+            _ptr(pos), _ptr(scores_out), _ptr(keep_out), _ptr(scratch), scratch.numel(),
+            _stream(v.device, stream)))
+        return
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check("vd_evict_step", load().vd_evict_step(
         ctypes.byref(desc), _ptr(n_h), _ptr(b_h), VARIANTS[variant], _ptr(running_sum),

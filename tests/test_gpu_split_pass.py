@@ -1,0 +1,114 @@
+"""The pass with several workgroups per unit (``vd_evict_step_split``) against
+the one with a single workgroup, on the same inputs.  With a running sum the
+column sums are added in the same order, so everything agrees bit for bit;
+without one they are added in parts, which moves an fp64 mean by less than n *
+2^-53 of its terms, and an fp32 score by one rounding at most.  Sizes sit where
+the split count changes, at shares of less than a row group and of no row, at
+the edges of the staging (all, some and none of the new rows in LDS), at a
+single eviction, at units that do not evict, and at the slot limit."""
+import ctypes
+import os
+
+import pytest
+import torch
+
+from paper_2609_23314_amd import build as lib_build
+from paper_2609_23314_amd import synth, vd
+from paper_2609_23314_amd.driver import EvictingCache
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(params=["release", "debug"])
+def library(request):
+    saved = (vd._lib, vd.LIB_PATH)
+    if request.param == "debug":
+        assert os.path.exists(lib_build.DEBUG_LIB), "build the debug library first"
+        vd._lib, vd.LIB_PATH = None, lib_build.DEBUG_LIB
+    lib = vd.load()
+    yield lib if request.param == "debug" else None
+    vd._lib, vd.LIB_PATH = saved
+
+
+def lds_word(library):
+    if library is None:
+        return 0
+    word = ctypes.c_uint32(0)
+    library.vd_debug_take_error_word.argtypes = [ctypes.c_void_p]
+    assert library.vd_debug_take_error_word(ctypes.byref(word)) == vd.VD_OK
+    return word.value
+
+
+# units as (L, H); n, N and what the state covers, per sequence
+SHAPES = [((1, 1), [2100], [2000], [2000]), ((3, 5), [1300, 700, 0], [1000, 800, 4], [1000, 650, 0]),
+          ((4, 8), [2049, 1025, 40], [2048, 1024, 40], [2048, 1024, 39]),
+          ((2, 4), [1500, 1201, 900], [400, 1200, 899], [0, 1201, 700]),
+          ((8, 16), [4097], [3000], [3000]), ((1, 3), [16384], [16383], [16383]), ((1, 2), [16384], [8000], [8000])]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("variant", ["l2", "dir", "norm", "key_norm"])
+@pytest.mark.parametrize("D,shape,ties,state", [(D, s, False, True) for D in (64, 128, 256) for s in SHAPES] +
+                         [(128, SHAPES[1], True, True)] + [(D, s, False, False) for D in (64, 256) for s in SHAPES[:5]])
+def test_split_matches_whole(library, dtype, variant, D, shape, ties, state):
+    (L, H), n, N, count = shape
+    S, C = len(n), min(max(n) + 3, 16384)
+    U = S * L * H
+    k, v = [synth.random_rows((S, L, H, C, D), dtype, 17 + i, DEV) for i in range(2)]
+    if ties:
+        k, v = [x[:, :, :, :1].expand(-1, -1, -1, C, -1).contiguous() for x in (k, v)]
+        v[:, :, :, 5::40] *= 2
+        k[:, :, :, 7::50] *= 2
+    scored = k if variant.startswith("key") else v
+    sums = torch.zeros((S, L, H, D + 1), dtype=torch.float64, device=DEV) if state else None
+    for s in range(S if state else 0):
+        sums[s, ..., :D] = scored[s, :, :, :count[s]].double().sum(2)
+        sums[s, ..., D] = count[s]
+    size = vd.vd_evict_step_split_size(v, k)
+    assert size > 0
+    scratch = torch.full((size,), 0xFF, dtype=torch.uint8, device=DEV)
+    runs = []
+    for use in (None, scratch):
+        a = dict(k=k.clone(), v=v.clone(), pos=torch.arange(C, dtype=torch.int32, device=DEV).repeat(U, 1),
+                 scores=torch.zeros((U, C), device=DEV), keep=torch.zeros((U, C), dtype=torch.uint8, device=DEV))
+        a["sums"] = sums.clone().view(U, -1) if state else None
+        vd.vd_evict_step(a["k"], a["v"], n, N, variant, running_sum=a["sums"], pos=a["pos"], scores_out=a["scores"],
+                         keep_out=a["keep"], scratch=use)
+        assert lds_word(library) == 0
+        runs.append(a)
+    ref, got = runs
+    assert torch.allclose(got["scores"], ref["scores"], rtol=0 if state else 2e-7, atol=0)
+    for x in ("k", "v", "pos", "keep") + (("sums",) if state else ()):
+        assert torch.equal(got[x], ref[x]), x
+
+
+def test_scratch_is_checked():
+    k, v = torch.zeros((2, 1, 1, 2, 4096, 128), dtype=torch.bfloat16, device=DEV)
+    size = vd.vd_evict_step_split_size(v, k)
+    assert size > 0
+    for scratch in (torch.zeros(size - 1, dtype=torch.uint8, device=DEV),
+                    torch.zeros(size + 16, dtype=torch.uint8, device=DEV)[1:]):
+        with pytest.raises(vd.VdError, match="workspace"):
+            vd.vd_evict_step(k, v, [4000], [3000], scratch=scratch)
+    k, v = torch.zeros((2, 1, 16, 16, 512, 64), dtype=torch.bfloat16, device=DEV)
+    assert vd.vd_evict_step_split_size(v, k) == 0
+
+
+def test_cache_across_streams():
+    """A cache's passes on two streams, ordered by the caller, share its scratch."""
+    def run(streams):
+        cache = EvictingCache(1, 2, 2, 128, 2304, [2048])
+        for b in range(12):
+            rows = [synth.random_rows((2, 2, 256, 128), torch.bfloat16, 2 * b + i, DEV) for i in range(2)]
+            cache.append(0, *rows)
+            s = streams[b % len(streams)]
+            if s is not None:
+                s.wait_stream(torch.cuda.current_stream())
+            cache.evict(stream=s)
+            if s is not None:
+                torch.cuda.current_stream().wait_stream(s)
+        return cache
+    a, b = run([None]), run([torch.cuda.Stream(), None, torch.cuda.Stream()])
+    for x, y in ((a.k, b.k), (a.v, b.v), (a.pos, b.pos), (a.running_sum, b.running_sum)):
+        assert torch.equal(x, y)
