@@ -108,25 +108,31 @@ def _dtype_code(t):
 
 def cache_desc(v, k=None, num_q_heads=None) -> VdCacheDesc:
     """Descriptor of a 5-D ``[seq, layer, kv_head, slot, head_dim]`` cache view."""
-    if v.dim() != 5:
+    shape, strides = v.shape, v.stride()
+    if len(shape) != 5:
         raise ValueError("v must be a 5-D [seq, layer, kv_head, slot, head_dim] view")
-    if v.stride(4) != 1:
+    if strides[4] != 1:
         raise ValueError("the head_dim stride must be 1")
-    if k is not None and (k.shape != v.shape or k.stride() != v.stride() or k.dtype != v.dtype):
+    if k is not None and (k.shape != shape or k.stride() != strides or k.dtype != v.dtype):
         raise ValueError("k must match v in shape, strides and dtype")
-    S, L, H, C, Dh = v.shape
-    d = VdCacheDesc()
-    d.k = k.data_ptr() if k is not None else None
-    d.v = v.data_ptr()
-    d.dtype = _dtype_code(v)
-    d.num_seqs, d.num_layers, d.num_kv_heads = S, L, H
-    d.num_q_heads = H if num_q_heads is None else int(num_q_heads)
-    d.head_dim, d.capacity = Dh, C
-    d.stride_seq, d.stride_layer, d.stride_head, d.stride_slot = v.stride()[:4]
-    return d
+    S, L, H, C, Dh = shape
+    return VdCacheDesc(None if k is None else k.data_ptr(), v.data_ptr(), _dtype_code(v), S, L, H,
+                       H if num_q_heads is None else int(num_q_heads), Dh, C, *strides[:4])
 
+
+# The host's work for a small pass takes longer than the GPU's (an append and a
+# pass over one unit: 33 us against 10), so the few helpers that every call goes
+# through keep to plain Python objects: a descriptor filled by its constructor, a
+# list of ints as a C array rather than a tensor, the current stream's handle
+# without a Stream object (append and pass of one unit 33 -> 24 us, of 32 units 33 -> 27).
 
 def _host_i32(x, S, name):
+    """One int32 per sequence as a host array (a ctypes one where x is a list or
+    tuple of ints, else a tensor, which converts what torch converts)."""
+    if type(x) in (list, tuple) and all(type(i) is int and -2 ** 31 <= i < 2 ** 31 for i in x):
+        if len(x) != S:
+            raise ValueError(f"{name} must have one entry per sequence ({S})")
+        return (ctypes.c_int32 * S)(*x)
     t = torch.as_tensor(x, dtype=torch.int32).reshape(-1).cpu().contiguous()
     if t.numel() != S:
         raise ValueError(f"{name} must have one entry per sequence ({S})")
@@ -134,10 +140,14 @@ def _host_i32(x, S, name):
 
 
 def _ptr(t):
-    return None if t is None else t.data_ptr()
+    if t is None:
+        return None
+    return ctypes.addressof(t) if isinstance(t, ctypes.Array) else t.data_ptr()
 
 
 def _stream(dev, stream):
+    if stream is None and dev.type == "cuda" and dev.index is not None:
+        return torch._C._cuda_getCurrentRawStream(dev.index)
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     return s.cuda_stream
 
@@ -242,9 +252,14 @@ def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=Non
         _stream(v.device, stream)))
 
 
-def _append_rows_ok(x, like, L, H, D):
-    return (type(x) is torch.Tensor and x.dtype == like.dtype and x.device == like.device and x.dim() == 4
-            and x.shape[0] == L and x.shape[1] == H and x.shape[3] == D and x.stride(3) == 1
+_Strides3 = ctypes.c_int64 * 3
+
+
+def _append_rows_ok(x, dtype, dev, L, H, D):
+    if not (type(x) is torch.Tensor and x.dtype == dtype and x.device == dev):
+        return False
+    shape = x.shape
+    return (len(shape) == 4 and shape[0] == L and shape[1] == H and shape[3] == D and x.stride(3) == 1
             and not x.requires_grad and not x.is_neg())
 
 
@@ -254,30 +269,32 @@ def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
     library took the call; False, with nothing queued, for rows or caches that
     are not what its kernel reads (another dtype, device or layout, rows that
     overlap the cache), which a caller then copies with torch."""
-    if not (type(k) is torch.Tensor and type(v) is torch.Tensor and v.is_cuda and v.dim() == 5 and v.stride(4) == 1
-            and k.shape == v.shape and k.stride() == v.stride() and k.dtype == v.dtype and k.device == v.device
-            and v.dtype in (torch.bfloat16, torch.float32)):
+    if not (type(k) is torch.Tensor and type(v) is torch.Tensor and v.is_cuda):
+        return False
+    shape, strides, dtype, dev = v.shape, v.stride(), v.dtype, v.device
+    if not (len(shape) == 5 and strides[4] == 1 and k.shape == shape and k.stride() == strides and k.dtype == dtype
+            and k.device == dev and dtype in (torch.bfloat16, torch.float32)):
         return False
     if k.requires_grad or v.requires_grad or k.is_neg() or v.is_neg():
         return False
     if (k.is_inference() or v.is_inference()) and not torch.is_inference_mode_enabled():
         return False
-    S, L, H, C, D = v.shape
+    S, L, H, C, D = shape
     seq, n_old, pos0 = int(seq), int(n_old), int(pos0)
-    if not (_append_rows_ok(k_rows, k, L, H, D) and _append_rows_ok(v_rows, v, L, H, D)
-            and k_rows.shape[2] == v_rows.shape[2] and k_rows.shape[2] > 0 and 0 <= seq < S
-            and 0 <= n_old <= C and 0 <= pos0 < 2 ** 31):
+    if not (_append_rows_ok(k_rows, dtype, dev, L, H, D) and _append_rows_ok(v_rows, dtype, dev, L, H, D)):
         return False
-    if pos is not None and not (type(pos) is torch.Tensor and pos.dtype == torch.int32 and pos.device == v.device
+    t = k_rows.shape[2]
+    if not (v_rows.shape[2] == t and t > 0 and 0 <= seq < S and 0 <= n_old <= C and 0 <= pos0 < 2 ** 31):
+        return False
+    if pos is not None and not (type(pos) is torch.Tensor and pos.dtype == torch.int32 and pos.device == dev
                                 and pos.shape == (S * L * H, C) and pos.is_contiguous()):
         return False
-    if v.device.index != torch.cuda.current_device():
+    if dev.index != torch.cuda.current_device():
         return False
-    strides = ctypes.c_int64 * 3
-    ks, vs = strides(*k_rows.stride()[:3]), strides(*v_rows.stride()[:3])
-    desc = cache_desc(v, k)
-    st = load().vd_append(ctypes.byref(desc), seq, n_old, k_rows.shape[2], k_rows.data_ptr(), ks,
-                          v_rows.data_ptr(), vs, _ptr(pos), pos0, _stream(v.device, None))
+    ks, vs = _Strides3(*k_rows.stride()[:3]), _Strides3(*v_rows.stride()[:3])
+    desc = VdCacheDesc(k.data_ptr(), v.data_ptr(), _dtype_code(v), S, L, H, H, D, C, *strides[:4])
+    st = load().vd_append(ctypes.byref(desc), seq, n_old, t, k_rows.data_ptr(), ks,
+                          v_rows.data_ptr(), vs, _ptr(pos), pos0, _stream(dev, None))
     if st in (VD_ERR_INVALID_ARG, VD_ERR_UNSUPPORTED):
         return False
     _check("vd_append", st)
@@ -337,8 +354,8 @@ def vd_decode_attention_evict(k, v, q, n_valid, budget, running_sum, scale=None,
     q's shape).  K, V, pos and the running sum are updated in place.  variant is
     "l2" (ValueDiff) or "fastcaote"."""
     desc, n_h, b_h, out = _decode_args(k, v, q, n_valid, budget, running_sum, pos, out)
-    ws_need = int(load().vd_decode_attention_workspace_size(ctypes.byref(desc), VARIANTS[variant]))
     if workspace is None:
+        ws_need = int(load().vd_decode_attention_workspace_size(ctypes.byref(desc), VARIANTS[variant]))
         workspace = torch.zeros(max(ws_need, 16), dtype=torch.uint8, device=v.device)
     ws_bytes = workspace.numel() * workspace.element_size()
     sc = float(v.shape[4]) ** -0.5 if scale is None else float(scale)
