@@ -40,19 +40,22 @@ def lds_word(library):
     return word.value
 
 
-# units as (L, H); n, N and what the state covers, per sequence
-SHAPES = [((1, 1), [2100], [2000], [2000]), ((3, 5), [1300, 700, 0], [1000, 800, 4], [1000, 650, 0]),
-          ((4, 8), [2049, 1025, 40], [2048, 1024, 40], [2048, 1024, 39]),
-          ((2, 4), [1500, 1201, 900], [400, 1200, 899], [0, 1201, 700]),
-          ((8, 16), [4097], [3000], [3000]), ((1, 3), [16384], [16383], [16383]), ((1, 2), [16384], [8000], [8000])]
+# units as (L, H); n, N and what the state covers, per sequence, from the rows R
+# that the longest unit has to have for a split, at least
+SHAPES = [lambda R: ((1, 1), [R + 5], [R - 95], [R - 95]),
+          lambda R: ((3, 5), [R + 300, R // 2, 0], [R, R // 2 + 100, 4], [R, R // 2 - 50, 0]),
+          lambda R: ((4, 8), [R + 1, R // 2 + 1, 40], [R, R // 2, 40], [R, R // 2, 39]),
+          lambda R: ((2, 4), [R, R - 299, 900], [400, R - 300, 899], [0, R - 299, 700]),
+          lambda R: ((8, 16), [2 * R + 1], [R + R // 2], [R + R // 2]),
+          lambda R: ((1, 3), [16384], [16383], [16383]), lambda R: ((1, 2), [16384], [8000], [8000])]
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("variant", ["l2", "dir", "norm", "key_norm"])
-@pytest.mark.parametrize("D,shape,ties,state", [(D, s, False, True) for D in (64, 128, 256) for s in SHAPES] +
-                         [(128, SHAPES[1], True, True)] + [(D, s, False, False) for D in (64, 256) for s in SHAPES[:5]])
+@pytest.mark.parametrize("D,shape,ties,state", [(D, i, False, True) for D in (64, 128, 256) for i in range(7)] +
+                         [(128, 1, True, True)] + [(D, i, False, False) for D in (64, 256) for i in range(5)])
 def test_split_matches_whole(library, dtype, variant, D, shape, ties, state):
-    (L, H), n, N, count = shape
+    (L, H), n, N, count = SHAPES[shape](768 * 1024 // (D * dtype.itemsize))
     S, C = len(n), min(max(n) + 3, 16384)
     U = S * L * H
     k, v = [synth.random_rows((S, L, H, C, D), dtype, 17 + i, DEV) for i in range(2)]
@@ -84,7 +87,7 @@ def test_split_matches_whole(library, dtype, variant, D, shape, ties, state):
 
 
 def test_scratch_is_checked():
-    k, v = torch.zeros((2, 1, 1, 2, 4096, 128), dtype=torch.bfloat16, device=DEV)
+    k, v = torch.zeros((2, 1, 1, 2, 4096, 128), dtype=torch.bfloat16, device=DEV)  # 1 MB a unit
     size = vd.vd_evict_step_split_size(v, k)
     assert size > 0
     for scratch in (torch.zeros(size - 1, dtype=torch.uint8, device=DEV),
@@ -98,8 +101,8 @@ def test_scratch_is_checked():
 def test_cache_across_streams():
     """A cache's passes on two streams, ordered by the caller, share its scratch."""
     def run(streams):
-        cache = EvictingCache(1, 2, 2, 128, 2304, [2048])
-        for b in range(12):
+        cache = EvictingCache(1, 2, 2, 128, 3328, [3072])
+        for b in range(16):
             rows = [synth.random_rows((2, 2, 256, 128), torch.bfloat16, 2 * b + i, DEV) for i in range(2)]
             cache.append(0, *rows)
             s = streams[b % len(streams)]
