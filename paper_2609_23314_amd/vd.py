@@ -25,7 +25,8 @@ VARIANTS = {"l2": 0, "dir": 1, "norm": 2, "key_l2": 3, "key_dir": 4, "key_norm":
 MAX_CAPACITY = 16384
 
 EXPORTS = ("vd_score", "vd_select_topn", "vd_compact", "vd_evict_step",
-           "vd_evict_step_workspace_size", "vd_status_string", "vd_stream_read",
+           "vd_evict_step_workspace_size", "vd_evict_step_split",
+           "vd_evict_step_split_size", "vd_status_string", "vd_stream_read",
            "vd_append", "vd_geometry", "vd_decode_attention_evict", "vd_decode_attention_workspace_size",
            "vd_decode_attention_evict_noalloc", "vd_decode_attention_noalloc_max_bytes")
 
