@@ -298,12 +298,11 @@ vd_status evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const in
             if ((st = plan_step_lds(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, vd::kBlock,
                                     vd::kLdsBytes, false, lds)) != VD_OK)
                 return st;
-            st = launched(vd::launch_split_step(p, ns, desc->dtype, desc->head_dim, variant, lds, stream));
         } else {
             if ((st = plan_step(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, lds)) != VD_OK)
                 return st;
-            st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds, stream));
         }
+        st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds, stream));
         if (st != VD_OK) return st;
     }
     return VD_OK;
@@ -462,7 +461,17 @@ vd_status vd_geometry(const vd_cache_desc *desc, const int32_t *n_valid, const d
         p.v_sum = v_sum;
         p.off_keys = int32_t(sizeof(vd::LdsHead));
         p.off_lists = int32_t(p.off_keys + red_bytes);
-        const size_t lds = size_t(p.off_lists + ctr_bytes);
+        // the first bf16 rows of K and V stay in LDS from one stream to the other, in whole tiles
+        const int64_t tile_bytes = 2 * vd::kGeoRows * int64_t(vd::kBlock) * 16;
+        const int64_t tile_rows = tile_bytes / (2 * int64_t(desc->head_dim) * elem_bytes(desc->dtype));
+        int nmax = 0;
+        for (int i = 0; i < ns; ++i) nmax = std::max(nmax, p.nN[2 * i]);
+        p.off_stash = int32_t(p.off_lists + ctr_bytes);
+        const int64_t tiles = k_sum || desc->dtype != VD_DTYPE_BF16 ? 0
+                                              : std::min<int64_t>((vd::kLdsBytes - p.off_stash) / tile_bytes,
+                                                                  (nmax + tile_rows - 1) / tile_rows);
+        p.stash_rows = int32_t(tiles * tile_rows);
+        const size_t lds = size_t(p.off_stash + tiles * tile_bytes);
         st = launched(vd::launch_geometry(p, ns, desc->dtype, desc->head_dim, lds,
                                           reinterpret_cast<hipStream_t>(stream)));
         if (st != VD_OK) return st;

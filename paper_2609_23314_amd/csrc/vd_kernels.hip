@@ -1567,10 +1567,12 @@ template <int DT> __device__ __forceinline__ float row_elem(const char *row, int
 // in fp32 from the difference to the centroid held as an fp32 pair (hi +
 // lo), so that its error stays at fp32 rounding of the distance however far
 // the centroid lies from the origin; every sum over rows is fp64, in a fixed
-// order.  With two streams the first keeps the rows cacheable and the second
-// reads them once more, in reverse order and without retention.
-constexpr int kGeoRows = 2;  // rows per lane group in one tile of the geometry streams
-
+// order.  With two streams the first keeps the rows cacheable, and as many whole
+// tiles of bf16 rows as LDS has room for (128 KB) stay there; the second stream
+// reads the others once more, in reverse order and without retention.  Bound by
+// those two reads (256 units of 2560 rows, d = 128: 671 MB, 103.4 us at first, 100.5
+// with the held rows, 98 with four distances at a time; four rows per lane group in
+// flight instead of two took 119).
 template <int DT, int D>
 __global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
     using S = Shape<DT, D>;
@@ -1609,6 +1611,17 @@ __global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
         return row_off(min(max(e0, 0) + (j >> 1) * S::GROUPS + g, n - 1), ss32, cl) + z;
     };
 
+    // With two streams of bf16 rows the first `held` rows stay in LDS (each
+    // thread's own chunks), so that the second stream reads them there.  (The
+    // registers leave a CU one workgroup of bf16 rows at a time and two of fp32
+    // rows, which the LDS, and the registers that this and the bf16 loops below take,
+    // would make one: 576 units of 1000 fp32 rows, sums given, 104 -> 114 us.)
+    const int held = DT == 0 ? p.stash_rows : 0;  // a multiple of kTile
+    auto held_at = [&](int e0, int j) __attribute__((always_inline)) {
+        return reinterpret_cast<uint4 *>(lds + p.off_stash) +
+               lds_ix<kSiteStash>((e0 / kTile * 2 * kGeoRows + j) * NT + threadIdx.x, held * 2 * S::LPR);
+    };
+
     // ---- centroids: the caller's column sums when they cover the n rows,
     // else fp64 column sums of all n rows (a first stream) ----
     const double *ksu = p.k_sum ? p.k_sum + u * (D + 1) : nullptr;
@@ -1640,24 +1653,33 @@ __global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
             buf[j] = *reinterpret_cast<const uint4 *>(((j & 1) ? vb : kb) + chunk_off(0, j, 0u));
             __builtin_amdgcn_sched_barrier(0);  // issued in chunk order, as the loop reissues them
         }
-        for (int e0 = 0; e0 < n; e0 += kTile) {
+        // (only the last tile asks which of its rows exist)
+        auto sum_tile = [&](int e0, auto full) __attribute__((always_inline)) {
 #pragma unroll
             for (int r = 0; r < kGeoRows; ++r) {
                 float x[S::EPL], y[S::EPL];
                 E::unpack(buf[2 * r], x);
                 E::unpack(buf[2 * r + 1], y);
-                const bool valid = e0 + r * S::GROUPS + g < n;  // selects, not a branch
+                const bool valid = full() || e0 + r * S::GROUPS + g < n;  // selects, not a branch
 #pragma unroll
                 for (int i = 0; i < S::EPL; ++i) {
                     ak[i] += valid ? (double)x[i] : 0.0;
                     av[i] += valid ? (double)y[i] : 0.0;
+                }
+                if (e0 < held) {
+                    *held_at(e0, 2 * r) = buf[2 * r];
+                    *held_at(e0, 2 * r + 1) = buf[2 * r + 1];
                 }
                 const uint32_t z = zero_after(x[0] + y[0]);
                 buf[2 * r] = *reinterpret_cast<const uint4 *>(kb + chunk_off(e0 + kTile, 2 * r, z));
                 buf[2 * r + 1] = *reinterpret_cast<const uint4 *>(vb + chunk_off(e0 + kTile, 2 * r + 1, z));
                 __builtin_amdgcn_sched_barrier(0);
             }
-        }
+        };
+        int e0 = 0;
+        if constexpr (DT == 0)
+            for (; e0 + kTile <= n; e0 += kTile) sum_tile(e0, std::true_type{});
+        for (; e0 < n; e0 += kTile) sum_tile(e0, std::false_type{});
         const int red_cap = (p.off_lists - p.off_keys) / 8;
         sk = block_col_total<DT, D>(ak, red, red_cap);
         __syncthreads();  // every column total of K is read before red is refilled
@@ -1704,34 +1726,73 @@ __global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
         vl[i] = ctr[3 * D + c];
     }
     double s1k = 0.0, s2k = 0.0, s1v = 0.0, s2v = 0.0;
+    auto sq_dist = [&](uint4 w, const float (&hi)[S::EPL], const float (&lo)[S::EPL]) __attribute__((always_inline)) {
+        float x[S::EPL], d = 0.f;
+        E::unpack(w, x);
+#pragma unroll
+        for (int i = 0; i < S::EPL; ++i) {
+            const float t = (x[i] - hi[i]) - lo[i];
+            d = fmaf(t, t, d);
+        }
+        return d;
+    };
     // last tile first: the rows a first stream read most recently are the
     // likeliest still to be held in the caches
-    if (!given) first_distance_tile();
-    for (int e0 = last; e0 >= 0; e0 -= kTile) {
+    if constexpr (DT == 0) {
+        // Four distances at a time: lane c < 4 of a lane group ends with chunk
+        // quad_row(c)'s, a key row's if that is even.
+        static_assert(kGeoRows == 2, "four chunks at a time");
+        const int mine = quad_row(cl);
+        double s1 = 0.0, s2 = 0.0;
+        auto distances = [&](int e0, auto more) __attribute__((always_inline)) {
+            float a[4];
 #pragma unroll
-        for (int r = 0; r < kGeoRows; ++r) {
-            float x[S::EPL], y[S::EPL];
-            E::unpack(buf[2 * r], x);
-            E::unpack(buf[2 * r + 1], y);
-            float a = 0.f, b = 0.f;
-#pragma unroll
-            for (int i = 0; i < S::EPL; ++i) {
-                const float dx = (x[i] - kh[i]) - kl[i];
-                const float dy = (y[i] - vh[i]) - vl[i];
-                a = fmaf(dx, dx, a);
-                b = fmaf(dy, dy, b);
+            for (int j = 0; j < 4; ++j) {
+                a[j] = (j & 1) ? sq_dist(buf[j], vh, vl) : sq_dist(buf[j], kh, kl);
+                if constexpr (more()) {
+                    buf[j] = load_stream((j & 1) ? vb : kb, chunk_off(e0 - kTile, j, zero_after(a[j])));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            const uint32_t z = zero_after(a + b);
-            buf[2 * r] = load_stream(kb, chunk_off(e0 - kTile, 2 * r, z));
-            buf[2 * r + 1] = load_stream(vb, chunk_off(e0 - kTile, 2 * r + 1, z));
-            __builtin_amdgcn_sched_barrier(0);
-            const double dk = (double)score_sqrt(row_sum<S::LPR>(a));
-            const double dv = (double)score_sqrt(row_sum<S::LPR>(b));
-            const bool mine = cl == 0 && e0 + r * S::GROUPS + g < n;  // one lane per row
-            s1k += mine ? dk : 0.0;
-            s2k += mine ? dk * dk : 0.0;
-            s1v += mine ? dv : 0.0;
-            s2v += mine ? dv * dv : 0.0;
+            const double d = (double)score_sqrt(row_sums4<S::LPR>(a, cl));
+            if (cl < 4 && e0 + (mine >> 1) * S::GROUPS + g < n) {
+                s1 += d;
+                s2 += d * d;
+            }
+        };
+        const int held_rows = given ? 0 : min(held, last + kTile);
+        if (!given && last >= held_rows) first_distance_tile();
+        int e0 = last;
+        for (; e0 - kTile >= held_rows; e0 -= kTile) distances(e0, std::true_type{});
+        if (e0 >= held_rows) {
+            distances(e0, std::false_type{});
+            e0 -= kTile;
+        }
+        for (; e0 >= 0; e0 -= kTile) {
+#pragma unroll
+            for (int j = 0; j < 2 * kGeoRows; ++j) buf[j] = *held_at(e0, j);
+            distances(e0, std::false_type{});
+        }
+        ((mine & 1) ? s1v : s1k) = s1;
+        ((mine & 1) ? s2v : s2k) = s2;
+    } else {
+        if (!given) first_distance_tile();
+        for (int e0 = last; e0 >= 0; e0 -= kTile) {
+#pragma unroll
+            for (int r = 0; r < kGeoRows; ++r) {
+                const float a = sq_dist(buf[2 * r], kh, kl), b = sq_dist(buf[2 * r + 1], vh, vl);
+                const uint32_t z = zero_after(a + b);
+                buf[2 * r] = load_stream(kb, chunk_off(e0 - kTile, 2 * r, z));
+                buf[2 * r + 1] = load_stream(vb, chunk_off(e0 - kTile, 2 * r + 1, z));
+                __builtin_amdgcn_sched_barrier(0);
+                const double dk = (double)score_sqrt(row_sum<S::LPR>(a));
+                const double dv = (double)score_sqrt(row_sum<S::LPR>(b));
+                const bool mine = cl == 0 && e0 + r * S::GROUPS + g < n;  // one lane per row
+                s1k += mine ? dk : 0.0;
+                s2k += mine ? dk * dk : 0.0;
+                s1v += mine ? dv : 0.0;
+                s2v += mine ? dv * dv : 0.0;
+            }
         }
     }
     s1k = wave_sum_f64(s1k);
@@ -2640,9 +2701,11 @@ template <int DT> void *attn_kernel_for(int head_dim, int group, bool caote, boo
 // The ABI's variants onto the kernel's score forms (a key-side variant is the
 // value-side form on the rows the host passes in V's place).
 template <int DT, int D, int THREADS, int PART> void *step_kernel_for(int variant) {
+    // (the finishing part depends on the variant by its keys' order alone)
+    constexpr int kFirst = PART == kFinish ? kNorm : kL2, kSecond = PART == kFinish ? kNorm : kDir;
     switch (variant) {
-        case 0: case 3: return reinterpret_cast<void *>(&step_kernel<DT, D, kL2, THREADS, PART>);
-        case 1: case 4: return reinterpret_cast<void *>(&step_kernel<DT, D, kDir, THREADS, PART>);
+        case 0: case 3: return reinterpret_cast<void *>(&step_kernel<DT, D, kFirst, THREADS, PART>);
+        case 1: case 4: return reinterpret_cast<void *>(&step_kernel<DT, D, kSecond, THREADS, PART>);
         case 2: return reinterpret_cast<void *>(&step_kernel<DT, D, kNorm, THREADS, PART>);
         case 5: return reinterpret_cast<void *>(&step_kernel<DT, D, kKeepSmallest, THREADS, PART>);
     }
@@ -2650,8 +2713,6 @@ template <int DT, int D, int THREADS, int PART> void *step_kernel_for(int varian
 }
 
 template <int DT, int THREADS, int PART> void *step_kernel_for(int head_dim, int variant) {
-    // (the finishing part depends on the variant by its keys' order alone)
-    if (PART == kFinish) variant = variant == 5 ? 5 : 2;
     switch (head_dim) {
         case 64: return step_kernel_for<DT, 64, THREADS, PART>(variant);
         case 128: return step_kernel_for<DT, 128, THREADS, PART>(variant);
@@ -2690,15 +2751,7 @@ hipError_t launch(void *fn, int num_seqs, size_t lds_bytes, hipStream_t stream,
     return hipLaunchKernel(fn, grid, dim3(threads), args, lds_bytes, stream);
 }
 
-}  // namespace
-
-hipError_t launch_step(const UnitParams &p, int num_seqs, int dtype, int head_dim,
-                       int variant, size_t lds_bytes, hipStream_t stream) {
-    void *fn = p.threads == kHalfBlock ? step_kernel_for<kHalfBlock, kWhole>(dtype, head_dim, variant)
-                                       : step_kernel_for<kBlock, kWhole>(dtype, head_dim, variant);
-    return launch(fn, num_seqs, lds_bytes, stream, p, p.threads);
-}
-
+// The pass by p.splits workgroups per unit, then one.
 hipError_t launch_split_step(const UnitParams &p, int num_seqs, int dtype, int head_dim, int variant,
                              size_t lds_bytes, hipStream_t stream) {
     void *rows = step_kernel_for<kBlock, kRows>(dtype, head_dim, variant);
@@ -2712,6 +2765,16 @@ hipError_t launch_split_step(const UnitParams &p, int num_seqs, int dtype, int h
     if (e == hipSuccess) e = hipLaunchKernel(rows, grid, dim3(NT), args, lds_bytes, stream);
     if (e != hipSuccess) return e;
     return launch(finish, num_seqs, size_t(p.off_stash), stream, p);
+}
+
+}  // namespace
+
+hipError_t launch_step(const UnitParams &p, int num_seqs, int dtype, int head_dim,
+                       int variant, size_t lds_bytes, hipStream_t stream) {
+    if (p.splits > 1) return launch_split_step(p, num_seqs, dtype, head_dim, variant, lds_bytes, stream);
+    void *fn = p.threads == kHalfBlock ? step_kernel_for<kHalfBlock, kWhole>(dtype, head_dim, variant)
+                                       : step_kernel_for<kBlock, kWhole>(dtype, head_dim, variant);
+    return launch(fn, num_seqs, lds_bytes, stream, p, p.threads);
 }
 
 hipError_t launch_select(const UnitParams &p, int num_seqs, size_t lds_bytes,

@@ -13,6 +13,7 @@ constexpr int kHalfBlock = kBlock / 2;    // the pass with two workgroups per CU
 constexpr int kCus = 256;                 // compute units of an MI355X
 constexpr int kMaxSeqsPerLaunch = 256;    // per-sequence n and N travel as kernel arguments
 constexpr int kLdsBytes = 160 * 1024;     // LDS of one gfx950 workgroup
+constexpr int kGeoRows = 2;               // geometry: rows of K and of V per lane group in one tile
 constexpr int kMaxSplitSlots = 16384;     // slots per unit of a split pass, at most
 
 enum Mode : int32_t { kModeStep = 0, kModeScore = 1 };
@@ -83,12 +84,10 @@ struct UnitParams {
     int32_t nN[2 * kMaxSeqsPerLaunch];   // n and N of each sequence of the launch, interleaved
 };
 
-// Each launches one workgroup per unit of `num_seqs` sequences.
+// Each launches one workgroup per unit of `num_seqs` sequences (the pass, with
+// p.splits above one, that many for the rows' scores first; p.threads is kBlock).
 hipError_t launch_step(const UnitParams &p, int num_seqs, int dtype, int head_dim,
                        int variant, size_t lds_bytes, hipStream_t stream);
-// The same by p.splits workgroups per unit, then one (p.threads is kBlock).
-hipError_t launch_split_step(const UnitParams &p, int num_seqs, int dtype, int head_dim, int variant,
-                             size_t lds_bytes, hipStream_t stream);
 hipError_t launch_select(const UnitParams &p, int num_seqs, size_t lds_bytes,
                          hipStream_t stream);
 hipError_t launch_compact(const UnitParams &p, int num_seqs, int dtype, int head_dim,

@@ -123,6 +123,19 @@ def test_geometry_with_column_sums(orc, dt, D):
 
 
 @pytest.mark.parametrize("dt", list(DTYPES))
+@pytest.mark.parametrize("D", [64, 128, 256])
+def test_geometry_tile_edges(orc, dt, D):
+    """Units that end at and beside the row tiles (64 KB of K and V), with all, some
+    and (the longest) few of their rows held in LDS between the two streams."""
+    T = 65536 // (2 * D * DTYPES[dt].itemsize)
+    n = [1, T - 1, T, T + 1, 2 * T, 2 * T + 1, 3 * T - 1, 5 * T]
+    k, v = make(len(n), 1, 1, 5 * T, D, DTYPES[dt], n, seed=77 + D)
+    check_units(orc, k, v, n, 1, 1)
+    for s in range(len(n)):  # a launch of one unit plans its LDS for that unit alone
+        check_units(orc, k[s:s + 1], v[s:s + 1], n[s:s + 1], 1, 1)
+
+
+@pytest.mark.parametrize("dt", list(DTYPES))
 def test_geometry_far_centroid(orc, dt):
     # rows far from the origin: the fp32 distance must not lose the spread
     n = [777]
