@@ -35,7 +35,6 @@ class EvictingCache:
         self.pos = (torch.full((self.units, capacity), -1, dtype=torch.int32, device=device)
                     if track_pos else None)
         self.capacity = capacity
-        self._scratch = None             # of the pass over few units, made by the first one
 
     def append(self, seq: int, k_rows: torch.Tensor, v_rows: torch.Tensor):
         """Appends [layers, kv_heads, t, head_dim] rows to sequence `seq`."""
@@ -62,30 +61,10 @@ class EvictingCache:
                                device=self.pos.device)
             self.pos[u0:u0 + L * H, n0:n0 + t] = ids
 
-    def _split_scratch(self, stream):
-        """The scratch of a pass over few units, for this cache alone, made on the
-        stream of its first pass; None where the pass takes none."""
-        key = (self.v.shape, self.v.dtype, self.v.device)
-        if self._scratch is None or self._scratch[0] != key:
-            size = vd.vd_evict_step_split_size(self.v, self.k)
-            at = buf = None
-            if size:
-                at = stream if stream is not None else torch.cuda.current_stream(self.v.device)
-                with torch.cuda.stream(at):
-                    buf = torch.empty(size, dtype=torch.uint8, device=self.v.device)
-                at = at.cuda_stream
-            self._scratch = key, buf, at
-        _, buf, at = self._scratch
-        if buf is not None:
-            run = stream if stream is not None else torch.cuda.current_stream(self.v.device)
-            if run.cuda_stream != at:
-                buf.record_stream(run)
-        return buf
-
     def evict(self, scores_out=None, keep_out=None, stream=None):
         """One eviction pass over every unit; afterwards n = min(n, N)."""
         vd.vd_evict_step(self.k, self.v, self.n, self.budget, self.variant,
                          running_sum=self.running_sum, pos=self.pos, scores_out=scores_out,
                          keep_out=keep_out, num_q_heads=self.num_q_heads, stream=stream,
-                         scratch=self._split_scratch(stream))
+                         scratch=True)
         self.n = [min(n, N) for n, N in zip(self.n, self.budget)]

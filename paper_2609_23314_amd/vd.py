@@ -220,13 +220,29 @@ def vd_evict_step_split_size(v, k=None):
     return int(load().vd_evict_step_split_size(ctypes.byref(desc)))
 
 
+def _call_scratch(size, dev, stream):
+    """``size`` bytes of torch's allocator for one call on its stream, which are
+    handed on in that stream's order once the call is queued (under capture they
+    come from the graph's own pool and live as long as the graph); None where
+    there is no memory for them."""
+    try:
+        if stream is None:
+            return torch.empty(size, dtype=torch.uint8, device=dev)
+        at = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, dev)
+        with torch.cuda.stream(at):
+            return torch.empty(size, dtype=torch.uint8, device=dev)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=None,
                   scores_out=None, keep_out=None, workspace=None, *, num_q_heads=None,
                   stream=None, scratch=None):
     """One eviction pass over every unit, in place (see ``vd_evict_step`` in vd.h).
     With ``scratch`` (a uint8 tensor of ``vd_evict_step_split_size`` bytes, not
-    shared by calls that overlap) a pass over few units spreads each of them
-    over several workgroups (``vd_evict_step_split`` in vd.h)."""
+    shared by calls that overlap, or True: the call takes its own from torch) a
+    pass over few units spreads each of them over several workgroups
+    (``vd_evict_step_split`` in vd.h)."""
     U, C, Dh = _units(v), v.shape[3], v.shape[4]
     desc = cache_desc(v, k, num_q_heads)
     n_h = _host_i32(n_valid, v.shape[0], "n_valid")
@@ -239,6 +255,9 @@ def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=Non
         _need(scores_out, "scores_out", torch.float32, U * C, v.device)
     if keep_out is not None:
         _need(keep_out, "keep_out", torch.uint8, U * C, v.device)
+    if scratch is True:
+        size = load().vd_evict_step_split_size(ctypes.byref(desc))
+        scratch = _call_scratch(size, v.device, stream) if size else None
     if scratch is not None:
         _need(scratch, "scratch", torch.uint8, 0, v.device)
         _check("vd_evict_step_split", load().vd_evict_step_split(

@@ -115,3 +115,56 @@ def test_cache_across_streams():
     a, b = run([None]), run([torch.cuda.Stream(), None, torch.cuda.Stream()])
     for x, y in ((a.k, b.k), (a.v, b.v), (a.pos, b.pos), (a.running_sum, b.running_sum)):
         assert torch.equal(x, y)
+
+
+def test_graph_outlives_its_cache():
+    """A captured pass writes to the cache's tensors and to memory of the graph's
+    own: with the cache object gone and the freed memory given to other tensors,
+    replays leave those alone and give the eager results."""
+    L, H, D, N, n = 2, 2, 128, 8000, 8192
+    cache = EvictingCache(1, L, H, D, n, [N], device=DEV)
+    size = vd.vd_evict_step_split_size(cache.v, cache.k)
+    assert size > 0
+    for x, seed in ((cache.k, 5), (cache.v, 6)):
+        x.copy_(synth.random_rows((1, L, H, n, D), torch.bfloat16, seed, DEV))
+    cache.running_sum.view(L * H, D + 1)[:, :D] = cache.v[0, :, :, :N].double().sum(2).view(L * H, D)
+    cache.running_sum.view(L * H, D + 1)[:, D] = N
+    cache.pos.copy_(torch.arange(n, dtype=torch.int32, device=DEV).expand(L * H, -1))
+    held = [cache.k, cache.v, cache.running_sum, cache.pos]
+    start = [x.clone() for x in held]
+    cache.n = [n]
+    cache.evict()                               # eager
+    want = [x.clone() for x in held]
+    cache.n = [n]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cache.evict()
+    del cache
+    others = [torch.full((size,), 7, dtype=torch.uint8, device=DEV) for _ in range(4)]
+    for rep in range(3):
+        for x, y in zip(held, start):
+            x.copy_(y)
+        work = torch.randn(1 << 20, device=DEV).sum()   # eager work between the replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(held, want)), (rep, float(work))
+        assert all(bool((x == 7).all()) for x in others), rep
+
+
+class _Handle:
+    """A stream known by its handle alone, as another library hands it over."""
+    def __init__(self, stream):
+        self.cuda_stream = stream.cuda_stream
+
+
+@pytest.mark.parametrize("wrap", [lambda s: s, _Handle], ids=["stream", "handle"])
+def test_call_takes_its_own_scratch(wrap):
+    k, v = [synth.random_rows((1, 2, 2, 6150, 64), torch.bfloat16, 3 + i, DEV) for i in range(2)]
+    ref = [k.clone(), v.clone()]
+    vd.vd_evict_step(*ref, [6150], [6000])
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    vd.vd_evict_step(k, v, [6150], [6000], scratch=True, stream=wrap(s))
+    torch.cuda.current_stream().wait_stream(s)
+    assert torch.equal(k, ref[0]) and torch.equal(v, ref[1])
