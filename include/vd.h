@@ -295,8 +295,8 @@ vd_status vd_decode_attention_evict_noalloc(const vd_cache_desc *desc, const flo
 size_t vd_decode_attention_noalloc_max_bytes(void);
 
 /* vd_evict_step with device scratch, through which several workgroups share the
- * rows of each unit where the cache has at most half as many units as the GPU
- * has compute units.  Arguments, results and errors are vd_evict_step's, and:
+ * rows of each unit where the cache has at most a quarter as many units as the
+ * GPU has compute units.  Arguments, results and errors are vd_evict_step's, and:
  *
  *   scratch      device, 16-byte aligned, at least vd_evict_step_split_size()
  *                bytes (may be NULL when that is 0), of any content; calls that

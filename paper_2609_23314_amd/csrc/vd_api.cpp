@@ -244,12 +244,17 @@ vd_status plan_step(const vd_cache_desc *d, UnitParams &p, int ns, bool score_mo
 // workgroup and split, us: 32 units of 2049 x 128 B 13.4 and 15.1, 1280 x 256 B
 // 17.4 and 20.1, 2560 x 256 B 24.6 and 22.7 (with its append 29.0 and 28.4, and the
 // host the slower of the two), 4096 x 256 B 32.2 and 23.8, 8193 x 256 B 45.8 and
-// 19.7; two splits of 128 units, 4096 x 256 B 40.5 and 39.6, 8193 x 256 B 58.3 and
-// 52.9.
+// 19.7.  Nor do fewer than kMinSplits splits: every split sums the unit's new rows
+// itself, and many units stream near the memory's rate by themselves.  Over sizes
+// (784 KB to 4 MB a unit), types and states, rows not in any cache, the split took
+// on average 0.74 of the time at 48 units, 0.79 at 64 (at most 1.04: all of 8192
+// fp32 rows new), 0.95 at 85 (up to 1.39) and 1.02 at 128 (up to 1.23).
 constexpr int64_t kSplitBytes = 64 * 1024, kSplitUnitBytes = 768 * 1024;
+constexpr int kMinSplits = 4;
 int max_splits(int64_t units) { return units > 0 ? int(std::min<int64_t>(64, vd::kCus / units)) : 0; }
 int step_splits(int64_t units, int64_t n, int64_t row_bytes) {
-    return n * row_bytes < kSplitUnitBytes ? 0 : int(std::min<int64_t>(max_splits(units), n * row_bytes / kSplitBytes));
+    if (n * row_bytes < kSplitUnitBytes || max_splits(units) < kMinSplits) return 0;
+    return int(std::min<int64_t>(max_splits(units), n * row_bytes / kSplitBytes));
 }
 // Scratch of a split pass: the keys, the column sums, the sums' partials.
 struct SplitWs {
@@ -287,7 +292,7 @@ vd_status evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const in
             splits = step_splits(step_units(desc), nmax, int64_t(desc->head_dim) * elem_bytes(desc->dtype));
         }
         size_t lds = 0;
-        if (splits > 1) {  // at most half as many units as CUs, so one launch holds them all
+        if (splits > 1) {  // at most a quarter as many units as CUs, so one launch holds them all
             const SplitWs ws = split_ws_layout(desc, step_units(desc));
             p.splits = splits;
             p.units = int32_t(step_units(desc));

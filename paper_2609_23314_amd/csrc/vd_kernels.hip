@@ -668,7 +668,7 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
 // ---------------------------------------------------------------- the pass
 
 // Parts of the pass: all of it in one workgroup per unit, or, where a launch
-// has at most half as many units as the chip has CUs, the rows' scores by
+// has at most a quarter as many units as the chip has CUs, the rows' scores by
 // p.splits workgroups per unit (kRows) and then the rest by one (kFinish).  A
 // single CU streams about 60 GB/s, so a launch of few units leaves the memory
 // idle: kRows spreads each unit's rows over the idle CUs.  Every kRows workgroup

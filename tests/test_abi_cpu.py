@@ -223,3 +223,12 @@ def test_decode_attention_workspace_sizes():
     assert l2 > 0
     assert lib.vd_decode_attention_workspace_size(ctypes.byref(d), 1) == 0      # not a decode score
     assert lib.vd_decode_attention_workspace_size(ctypes.byref(good_desc(head_dim=96)), 0) == 0
+
+
+@pytest.mark.parametrize("units", [1, 2, 51, 63, 64, 65, 85, 128, 129, 4096])
+@pytest.mark.parametrize("rows", [3071, 3072, 3136, 16384])
+def test_split_takes_few_units_of_many_bytes(units, rows):
+    """At least four workgroups per unit on 256 compute units, and 768 KB a unit."""
+    d = good_desc(num_seqs=1, num_layers=1, num_kv_heads=units, num_q_heads=units, capacity=rows,
+                  stride_head=rows * 128, stride_layer=units * rows * 128, stride_seq=units * rows * 128)
+    assert (vd.load().vd_evict_step_split_size(ctypes.byref(d)) > 0) == (units <= 64 and rows >= 3072)

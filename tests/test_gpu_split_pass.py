@@ -44,9 +44,9 @@ def lds_word(library):
 # that the longest unit has to have for a split, at least
 SHAPES = [lambda R: ((1, 1), [R + 5], [R - 95], [R - 95]),
           lambda R: ((3, 5), [R + 300, R // 2, 0], [R, R // 2 + 100, 4], [R, R // 2 - 50, 0]),
-          lambda R: ((4, 8), [R + 1, R // 2 + 1, 40], [R, R // 2, 40], [R, R // 2, 39]),
+          lambda R: ((4, 5), [R + 1, R // 2 + 1, 40], [R, R // 2, 40], [R, R // 2, 39]),
           lambda R: ((2, 4), [R, R - 299, 900], [400, R - 300, 899], [0, R - 299, 700]),
-          lambda R: ((8, 16), [2 * R + 1], [R + R // 2], [R + R // 2]),
+          lambda R: ((8, 8), [2 * R + 1], [R + R // 2], [R + R // 2]),
           lambda R: ((1, 3), [16384], [16383], [16383]), lambda R: ((1, 2), [16384], [8000], [8000])]
 
 
