@@ -15,6 +15,8 @@ import ctypes
 import os
 
 import torch
+from torch.autograd import forward_ad
+from torch.utils._device import DeviceContext
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libvd.so")
 
@@ -275,6 +277,21 @@ def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=Non
 _Strides3 = ctypes.c_int64 * 3
 
 
+_compiling, _tracing = torch.compiler.is_compiling, torch._C._is_tracing
+_dispatch_modes, _function_modes = torch._C._len_torch_dispatch_stack, torch._C._len_torch_function_stack
+_transform = torch._C._functorch.peek_interpreter_stack
+
+
+def _torch_follows():
+    """Whether torch itself follows what is done to tensors just now: a compile or a
+    trace, a dispatch or function mode (other than a default device's), a functorch
+    transform, a forward-mode level.  A kernel launched past torch would escape it."""
+    return (_compiling() or _tracing() or _dispatch_modes() > 0 or forward_ad._current_level >= 0
+            or _transform() is not None
+            or (_function_modes() > 0 and
+                any(type(m) is not DeviceContext for m in torch.overrides._get_current_function_mode_stack())))
+
+
 def _append_rows_ok(x, dtype, dev, L, H, D):
     if not (type(x) is torch.Tensor and x.dtype == dtype and x.device == dev):
         return False
@@ -288,7 +305,10 @@ def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
     their indices pos0 + r into ``pos``, on the current stream.  True if the
     library took the call; False, with nothing queued, for rows or caches that
     are not what its kernel reads (another dtype, device or layout, rows that
-    overlap the cache), which a caller then copies with torch."""
+    overlap the cache) or while torch follows copies (a transform, a trace, a
+    mode), which a caller then makes with torch."""
+    if _torch_follows():
+        return False
     if not (type(k) is torch.Tensor and type(v) is torch.Tensor and v.is_cuda):
         return False
     shape, strides, dtype, dev = v.shape, v.stride(), v.dtype, v.device
