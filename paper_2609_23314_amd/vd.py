@@ -317,7 +317,7 @@ def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
         return False
     if k.requires_grad or v.requires_grad or k.is_neg() or v.is_neg():
         return False
-    if (k.is_inference() or v.is_inference()) and not torch.is_inference_mode_enabled():
+    if (k.is_inference() or v.is_inference() or (pos is not None and pos.is_inference())) and not torch.is_inference_mode_enabled():
         return False
     S, L, H, C, D = shape
     seq, n_old, pos0 = int(seq), int(n_old), int(pos0)
@@ -338,6 +338,8 @@ def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
     if st in (VD_ERR_INVALID_ARG, VD_ERR_UNSUPPORTED):
         return False
     _check("vd_append", st)
+    # torch's backward refuses tensors whose version moved since it saved them
+    torch._C._increment_version((k, v) if pos is None else (k, v, pos))
     return True
 
 

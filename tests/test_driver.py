@@ -106,3 +106,34 @@ def test_append_takes_a_default_device():
     with torch.device("cuda"):
         assert vd.vd_append(cache.k, cache.v, 0, 0, rows, rows, cache.pos, 0)
     assert torch.equal(cache.k[0, :, :, :6], rows)
+
+
+@pytest.mark.parametrize("device", DEVICES)
+def test_append_counts_as_an_inplace_change(device):
+    """Each append moves the version counters as torch's copies do, so that a backward
+    through rows saved before it is refused instead of reading the changed ones."""
+    rows, cache = _new_rows(device), _cache(device)
+    cache.append(0, rows, rows)
+    w = torch.ones((), device=device, requires_grad=True)
+    products = [(x * w).sum() for x in (cache.k, cache.v)]
+    before = [x._version for x in (cache.k, cache.v, cache.pos)]
+    cache.append(0, rows, rows)
+    assert all(x._version > b for x, b in zip((cache.k, cache.v, cache.pos), before))
+    for y in products:
+        with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+            y.backward()
+
+
+@pytest.mark.parametrize("device", DEVICES)
+def test_append_and_inference_tensors(device):
+    rows = _new_rows(device)
+    with torch.inference_mode():
+        cache = _cache(device)
+        cache.append(0, rows, rows)
+        assert torch.equal(cache.v[0, :, :, :6], rows)
+    with pytest.raises(RuntimeError, match="[Ii]nference"):
+        cache.append(0, rows, rows)
+    made = _cache(device)
+    with torch.inference_mode():
+        made.append(0, rows, rows)
+    assert torch.equal(made.k[0, :, :, :6], rows)
