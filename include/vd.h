@@ -184,7 +184,8 @@ vd_status vd_evict_step(const vd_cache_desc *desc, const int32_t *n_valid,
  *   v_strides
  *   pos         device int32 [U][capacity] or NULL: slot n_old + r of every
  *               unit of the sequence receives pos0 + r
- * The rows must not overlap the cache (VD_ERR_INVALID_ARG).
+ * The rows must not overlap the cache, and no two of its layers or KV heads may
+ * share their memory (stride 0; VD_ERR_INVALID_ARG).
  */
 vd_status vd_append(const vd_cache_desc *desc, int32_t seq, int32_t n_old, int32_t rows,
                     const void *k_rows, const int64_t *k_strides, const void *v_rows,

@@ -24,6 +24,8 @@ extern "C" vd_status vd_append(const vd_cache_desc *desc, int32_t seq, int32_t n
     const int64_t es = elem_bytes(desc->dtype);
     const int64_t L = desc->num_layers, H = desc->num_kv_heads;
     const int64_t units = L * H;
+    // units that share memory would be written at once
+    if ((L > 1 && desc->stride_layer == 0) || (H > 1 && desc->stride_head == 0)) return VD_ERR_INVALID_ARG;
     if (units > INT32_MAX / 2) return VD_ERR_UNSUPPORTED;
     vd::AppendParams p;
     std::memset(&p, 0, sizeof p);

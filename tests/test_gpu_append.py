@@ -101,3 +101,28 @@ def test_append_rejects_bad_arguments():
         assert call(**bad) == vd.VD_ERR_INVALID_ARG, bad
     d.head_dim = 96
     assert call() == vd.VD_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("stride", ["stride_layer", "stride_head"])
+def test_append_rejects_units_that_share_memory(stride):
+    d = vd.VdCacheDesc()
+    d.k, d.v = 0x7F0000000000, 0x7F0100000000
+    d.dtype, d.head_dim, d.capacity = vd.VD_DTYPE_BF16, 64, 32
+    d.num_seqs, d.num_layers, d.num_kv_heads, d.num_q_heads = 2, 3, 4, 4
+    d.stride_slot, d.stride_head, d.stride_layer, d.stride_seq = 64, 2048, 8192, 24576
+    setattr(d, stride, 0)
+    s = (ctypes.c_int64 * 3)(4096, 1024, 64)
+    assert vd.load().vd_append(ctypes.byref(d), 0, 0, 8, 0x7E0000000000, s, 0x7E0100000000, s, None, 0,
+                               None) == vd.VD_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("device", ["cpu", pytest.param("cuda", marks=gpu)])
+@pytest.mark.parametrize("shape", [(1, 1, 3), (1, 2, 1)])
+def test_append_to_an_expanded_cache_is_refused(device, shape):
+    """As torch refuses to copy into memory that several units share."""
+    cache = EvictingCache(1, 2, 3, 64, 40, [40], dtype=torch.float32, device=device)
+    cache.k, cache.v = [torch.zeros((*shape, 40, 64), device=device).expand(1, 2, 3, 40, 64) for _ in range(2)]
+    rows = torch.ones((2, 3, 4, 64), device=device)
+    with pytest.raises(RuntimeError, match="single memory location"):
+        cache.append(0, rows, rows)
+    assert cache.n == [0] and cache.seen == [0] and not cache.k.any() and not cache.v.any()
