@@ -63,11 +63,11 @@ void hand_scored_rows(UnitParams &p, vd_variant variant) {
 }
 
 // Plans the dynamic LDS of the pass kernel for one launch, with `threads` per
-// workgroup and at most `limit` bytes; with `stage_all` only if every row to
-// stage fits.
+// workgroup and at most `limit` bytes, and fp64 sums of `red_waves` waves side by
+// side; with `stage_all` only if every row to stage fits.
 vd_status plan_step_lds(const vd_cache_desc *d, UnitParams &p, int ns, bool score_mode,
                         bool have_state, bool want_scores, int threads, int64_t limit,
-                        bool stage_all, size_t &lds_bytes) {
+                        int red_waves, bool stage_all, size_t &lds_bytes) {
     const int64_t row_bytes = int64_t(d->head_dim) * elem_bytes(d->dtype);
     int nmax = 0, keys_cap = 0, evict_cap = 0, move_cap = 0, want_rows = 0;
     for (int i = 0; i < ns; ++i) {
@@ -85,7 +85,7 @@ vd_status plan_step_lds(const vd_cache_desc *d, UnitParams &p, int ns, bool scor
     }
     // keys, then (when the unit selects) the second histogram buffer (a bin per
     // thread); the fp64 reduction scratch aliases the region
-    const int64_t red_bytes = int64_t(threads / 64) * d->head_dim * 8;
+    const int64_t red_bytes = int64_t(red_waves) * d->head_dim * 8;
     const int64_t sel_bytes = keys_cap > 0 ? align16(int64_t(keys_cap) * 4) + int64_t(threads) * 4 : 0;
     const int64_t keys_bytes = align16(std::max<int64_t>(sel_bytes, red_bytes));
     const int64_t lists_bytes = align16(int64_t(evict_cap + move_cap) * 4);
@@ -219,8 +219,10 @@ vd_status launch_decode(const vd_cache_desc *desc, const float *q, float scale,
 // would otherwise be read twice (128-byte rows, the cheapest to read again and
 // as dear to score, gain without); a decode step's selection (one row at most)
 // is too short to hide.  Measured, full against half workgroups, 1024 bf16
-// units (us): d = 128, n = 320 39.4 and 26.1, n = 2176 113.3 and 107.7, n =
-// 4160 185 and 179; d = 64, n = 1152 49.0 and 36.6, n = 8492 (576
+// units that evict 64 rows, in no cache (us): d = 128, n = 80 37.2 and 23.4, n =
+// 320 45.7 and 29.7, n = 2176 122 and 113, n = 4160 203 and 196; d = 64, n = 1152
+// 62.2 and 40.1 (scores alone 54.8 and 41.8; of 288 units of 700 rows, which only
+// a whole LDS stages, 14.3 and 15.2, the most that is lost), n = 8492 (576
 // units, 208 of 300 rows staged) 150 and 139; with 200 of 512 rows
 // staged (n = 2560, d = 128) 132 and 156, with 176 of 256 (eight
 // ragged sequences) 339 and 352, with 74 of 1024 (d = 256) 268 and 302.
@@ -229,11 +231,15 @@ vd_status plan_step(const vd_cache_desc *d, UnitParams &p, int ns, bool score_mo
     const int64_t units = int64_t(ns) * d->num_layers * d->num_kv_heads;
     bool argmin = !score_mode;  // every unit evicts at most one row
     for (int i = 0; i < ns; ++i) argmin = argmin && p.nN[2 * i] - 1 <= p.nN[2 * i + 1];
-    if (units > vd::kCus && !argmin &&
-        plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kHalfBlock, vd::kLdsBytes / 2,
-                      d->head_dim * elem_bytes(d->dtype) > 128, lds_bytes) == VD_OK)
-        return VD_OK;
-    return plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kBlock, vd::kLdsBytes, false, lds_bytes);
+    if (units > vd::kCus && !argmin) {
+        const bool wide = d->head_dim * elem_bytes(d->dtype) > 128;
+        for (int red_waves : {vd::kWaves, vd::kHalfBlock / 64})  // room for all sums at once only if it costs nothing
+            if (plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kHalfBlock, vd::kLdsBytes / 2,
+                              red_waves, wide || red_waves == vd::kWaves, lds_bytes) == VD_OK)
+                return VD_OK;
+    }
+    return plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kBlock, vd::kLdsBytes, vd::kWaves, false,
+                         lds_bytes);
 }
 
 // Splits of a pass over `units` units of at most n rows: the workgroups that the
@@ -301,7 +307,7 @@ vd_status evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const in
             p.ws_part = reinterpret_cast<double *>(scratch + ws.part);
             p.keys_stride = ws.keys_stride;
             if ((st = plan_step_lds(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, vd::kBlock,
-                                    vd::kLdsBytes, false, lds)) != VD_OK)
+                                    vd::kLdsBytes, vd::kWaves, false, lds)) != VD_OK)
                 return st;
         } else {
             if ((st = plan_step(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, lds)) != VD_OK)

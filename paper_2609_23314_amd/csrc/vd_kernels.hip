@@ -278,7 +278,9 @@ __device__ __forceinline__ void store_stream(char *base, uint32_t off, uint4 v) 
 // instructions (within one unit in the last place) without the exact-rounding
 // fix-up sequence.  Subnormal inputs are scaled by 2^64 first, since the
 // hardware units do not take them.  Every score of the library goes through
-// these two, so the standalone and the fused paths agree bit for bit.
+// these two and every mean of the pass through block_col_total's order of sums,
+// so the standalone and the fused paths agree bit for bit, whatever their
+// workgroups.
 __device__ __forceinline__ float score_sqrt(float x) {
     const bool tiny = x < 1.17549435e-38f;  // below the smallest normal
     const float r = __builtin_amdgcn_sqrtf(tiny ? x * 18446744073709551616.0f : x);
@@ -343,10 +345,6 @@ template <int O> __device__ __forceinline__ float pair_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Column sums of per-lane fp64 partials (each lane holds EPL columns of its
-// chunk), in a fixed order: thread t < D receives the total of column t (no
-// other thread receives anything).  `red` holds NW*D doubles; the caller
-// orders any later reuse of it with a barrier of its own.
 // One step of a halving sum over the lane pairs (l, l ^ O), O = 16 or 32:
 // the lower lane of each pair keeps p, the upper one q, each summed over the
 // pair with the lower lane's value first (as xor_sum adds).
@@ -360,20 +358,20 @@ template <int O> __device__ __forceinline__ double pair_sum_split(double p, doub
     return __longlong_as_double(((unsigned long long)H[0] << 32) | L[0]) +
            __longlong_as_double(((unsigned long long)H[1] << 32) | L[1]);
 }
-template <int DT, int D, int THREADS = kBlock>
-__device__ __forceinline__ double block_col_total(double *acc, double *red, int red_cap) {
-    using S = Shape<DT, D, THREADS>;
-    constexpr int NT = THREADS, NW = NT / 64;
+// The column sums of one wave's row groups, from per-lane fp64 partials (each
+// lane holds EPL columns of its chunk), summed in halving steps (lanes 16
+// apart, then 32 apart), each lane keeping half of its columns per step, in the
+// same association and operand order as summing each column over the row
+// groups: give(t, s) for each column t that this lane kept.
+template <int DT, int D, typename Give> __device__ __forceinline__ void wave_col_totals(double *acc, Give give) {
+    using S = Shape<DT, D>;
     constexpr int E = S::EPL;
-    // The wave's row groups are summed in halving steps (lanes 16 apart, then
-    // 32 apart), each lane keeping half of its columns per step, in the same
-    // association and operand order as summing each column over the row
-    // groups; each lane then writes the totals of the columns it kept.
     if constexpr (S::LPR <= 8) {
 #pragma unroll
         for (int i = 0; i < E; ++i) acc[i] = xor_sum<8>(acc[i]);
     }
-    const int lane = lane_id(), w = wave_id();
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));  // (what follows from it is worked out here, not kept through the row stream)
     constexpr int M16 = S::LPR <= 16 ? E / 2 : E;      // columns kept after the step over lanes 16 apart
     constexpr int M32 = S::LPR <= 32 ? M16 / 2 : M16;  // and after the one over lanes 32 apart
     static_assert(M32 >= 1, "at least one column per lane");
@@ -387,14 +385,46 @@ __device__ __forceinline__ double block_col_total(double *acc, double *red, int 
     if constexpr (S::LPR <= 32) first += (lane >> 5) * M32;
     if (S::LPR > 8 || (lane & 8) == 0)  // lanes 8 apart hold the same totals
 #pragma unroll
-        for (int i = 0; i < M32; ++i) red[lds_ix<kSiteRed>(w * D + (lane % S::LPR) * E + first + i, red_cap)] = v32[i];
-    __syncthreads();
-    static_assert(D <= NT, "one thread per column");
+        for (int i = 0; i < M32; ++i) give((lane % S::LPR) * E + first + i, v32[i]);
+}
+
+// The workgroup's column sums, in a fixed order: thread t < D receives the
+// total of column t (no other thread receives anything).  The order is that of
+// kBlock threads whatever the workgroup's size, so that a unit's sums (and with
+// them its scores and its state) do not depend on what else its launch holds: a
+// lane group of a smaller workgroup stands for PARTS of the kBlock threads' lane
+// groups, part h for the one of wave h * NW + w, and keeps their partials apart
+// (acc[h]).  Parts at and above `live` hold no row and are left out.  `red` holds
+// NW * D doubles, or kWaves * D, which saves a barrier a part; the caller orders
+// any later reuse of it with a barrier of its own.
+template <int DT, int D, int PARTS, int E>
+__device__ __forceinline__ double block_col_total(double (&acc)[PARTS][E], double *red, int red_cap,
+                                                  int live = PARTS) {
+    static_assert(E == Shape<DT, D>::EPL, "one partial per column of the chunk");
+    constexpr int NW = kWaves / PARTS;
+    static_assert(D <= NW * 64, "one thread per column");
+    const bool once = PARTS > 1 && live > 1 && red_cap >= kWaves * D;  // every part has a place of its own
     double s = 0.0;
-    if (threadIdx.x < D) {
+    auto total = [&](int waves) __attribute__((always_inline)) {
+        __syncthreads();
+        if (threadIdx.x < D) {
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) s += red[lds_ix<kSiteRed>(ww * D + threadIdx.x, red_cap)];
+            for (int ww = 0; ww < waves; ++ww) s += red[lds_ix<kSiteRed>(ww * D + threadIdx.x, red_cap)];
+        }
+    };
+#pragma unroll
+    for (int h = 0; h < PARTS; ++h) {
+        if (h >= live) continue;
+        if (h > 0 && !once) __syncthreads();
+        int at = wave_id();
+        asm volatile("" : "+v"(at));  // (as the lane above)
+        at = ((once ? h * NW : 0) + at) * D;
+        wave_col_totals<DT, D>(acc[h], [&](int t, double x) __attribute__((always_inline)) {
+            red[lds_ix<kSiteRed>(at + t, red_cap)] = x;
+        });
+        if (!once) total(NW);
     }
+    if (once) total(kWaves);
     return s;
 }
 
@@ -447,14 +477,14 @@ __device__ __forceinline__ uint32_t sum_below16(uint32_t x, int i) {
 // and K, ss: bytes per slot; null: no touch), so that the gather finds those
 // rows in L2.  The words land in tch, which the caller
 // keeps live until the gather is done (a register reused earlier would make
-// the wave wait for its load); only the sweep's first kTouchIters blocks of 64
+// the wave wait for its load); only the sweep's first TOUCH blocks of 64
 // slots touch.
-constexpr int kTouchIters = 4, kTouchLines = 2;
-template <int THREADS = kBlock>
+constexpr int kTouchLines = 2;
+template <int THREADS, int TOUCH>
 __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int N, uint32_t *evl, int evict_cap,
                                                 uint32_t *mvl, int move_cap, uint8_t *keep_out, LdsHead &H,
                                                 int keys_words, const char *tv, const char *tk, uint32_t ss,
-                                                int row_bytes, uint32_t (&tch)[kTouchIters][kTouchLines]) {
+                                                int row_bytes, uint32_t (&tch)[TOUCH][kTouchLines]) {
     constexpr int NW = THREADS / 64, BINS = THREADS, LOG_BINS = BINS == 1024 ? 10 : 9;
     static_assert(BINS == 1 << LOG_BINS && BINS <= kBins, "one histogram bin per thread");
     uint32_t *const hist2 = const_cast<uint32_t *>(keys) + ((n + 3) & ~3);
@@ -554,7 +584,7 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
         int jb = j0;
         if (tv) {
 #pragma unroll
-            for (int i = 0; i < kTouchIters; ++i, jb += 64)
+            for (int i = 0; i < TOUCH; ++i, jb += 64)
                 if (jb < j1) sweep(jb, BoolC<true>{}, tch[i]);
         }
         for (; jb < j1; jb += 64) sweep(jb, BoolC<false>{}, tch[0]);
@@ -680,10 +710,12 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
 // 45.8 -> 19.7 (one unit 40.4 -> 14.9); 36 units, d = 256, n = 5120, N = 4096 73.7 ->
 // 43.6; 32 units, d = 128, n = 8192 without a running sum 154 -> 93.
 enum : int { kWhole = 0, kRows = 1, kFinish = 2 };
+// (four waves per SIMD: one workgroup of kBlock threads per CU, or two of half as many)
 template <int DT, int D, int VAR, int THREADS, int PART = kWhole>
-__global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
+__global__ void __launch_bounds__(THREADS, 4) step_kernel(const UnitParams p) {
     using S = Shape<DT, D, THREADS>;
-    constexpr int NT = THREADS, NW = NT / 64;
+    constexpr int NT = THREADS, NW = NT / 64, PARTS = kBlock / THREADS;  // (PARTS: see block_col_total)
+    static_assert(kUnroll % PARTS == 0, "chunk k of every tile and batch belongs to part k % PARTS");
     using E = Elem<DT>;
     extern __shared__ __align__(16) unsigned char lds[];
     LdsHead &H = *reinterpret_cast<LdsHead *>(lds);
@@ -858,21 +890,23 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
     bool mean_zero = false;
 
     // ---- mean: sum the rows not yet summed (Sec. 3.2, Eq. vd) ----
-    double acc[S::EPL];
+    double acc[PARTS][S::EPL];
 #pragma unroll
-    for (int i = 0; i < S::EPL; ++i) acc[i] = 0.0;
-    auto mean_body = [&](int e, bool valid, uint4 w) __attribute__((always_inline)) {
+    for (int h = 0; h < PARTS; ++h)
+#pragma unroll
+        for (int i = 0; i < S::EPL; ++i) acc[h][i] = 0.0;
+    auto mean_body = [&](int e, bool valid, uint4 w, double (&a)[S::EPL]) __attribute__((always_inline)) {
         float x[S::EPL];
         E::unpack(w, x);
         if (valid) {
 #pragma unroll
-            for (int i = 0; i < S::EPL; ++i) acc[i] += (double)x[i];
+            for (int i = 0; i < S::EPL; ++i) a[i] += (double)x[i];
             if (e < staged)
                 *reinterpret_cast<uint4 *>(stash + (int64_t)lds_ix<kSiteStash>(e, p.stash_rows) * S::ROWB + cl * 16) = w;
         }
     };
     auto finish_mean = [&]() __attribute__((always_inline)) {
-        const double fresh_sum = block_col_total<DT, D, THREADS>(acc, red, red_cap);
+        const double fresh_sum = block_col_total<DT, D>(acc, red, red_cap, fresh > S::GROUPS ? PARTS : 1);
         if (threadIdx.x < D) {
             const int t = threadIdx.x;
             const double old_sum = count > 0 ? st_col : 0.0;
@@ -1028,9 +1062,9 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
 #pragma unroll
         for (int k = 0; k < kChunks; ++k) {
             const int e = t * kStep + k * NW * S::RPW + eb;
-            mean_body(e, e < fresh, buf[k]);
+            mean_body(e, e < fresh, buf[k], acc[k % PARTS]);
             if constexpr (more()) {
-                buf[k] = load_chunk(q, t + 1, k, zero_after(acc));
+                buf[k] = load_chunk(q, t + 1, k, zero_after(acc[k % PARTS]));
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1090,7 +1124,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
     } else {
         const int T = q.tiles;
         int t = 0;
-        if (q.small) mean_body(eb, eb < fresh, fc);
+        if (q.small) mean_body(eb, eb < fresh, fc, acc[0]);
         for (; t < q.tiles_f && t + 1 < T; ++t) use_fresh(t, std::true_type{});
         if (t < q.tiles_f) use_fresh(t++, std::false_type{});  // no scoring part follows
         finish_mean();
@@ -1147,6 +1181,8 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
 
     // ---- select (Sec. 2.1, Eq. eviction) ----
     int n_moves = 0;
+    // (a block fewer where the second set of partials needs the registers)
+    constexpr int kTouchIters = PARTS > 1 ? 3 : 4;
     uint32_t tch[kTouchIters][kTouchLines] = {};  // rows the selection fetched into L2 for the gather
     if (evict) {
         if (amode) {
@@ -1180,7 +1216,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
             __syncthreads();
         } else {
             (void)lds_ix<kSiteKeys>(n - 1, p.keys_cap);  // the keys fit their region
-            n_moves = select_and_build<THREADS>(keys, n, N, evl, p.evict_cap, mvl, p.move_cap, keep_out, H,
+            n_moves = select_and_build<THREADS, kTouchIters>(keys, n, N, evl, p.evict_cap, mvl, p.move_cap, keep_out, H,
                                        keys_words, vb, p.k ? p.k + off : nullptr, ss32, S::ROWB, tch);
         }
     } else {
@@ -1201,9 +1237,11 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
         auto vfetch = [&](int r) __attribute__((always_inline)) -> uint4 {
             return (r >= count && r < count + staged) ? sfetch(r, cl) : load_stream(vb, row_off(r, ss32, cl));
         };
-        double acc[S::EPL];
+        double acc[PARTS][S::EPL];
 #pragma unroll
-        for (int i = 0; i < S::EPL; ++i) acc[i] = 0.0;
+        for (int h = 0; h < PARTS; ++h)
+#pragma unroll
+            for (int i = 0; i < S::EPL; ++i) acc[h][i] = 0.0;
         if (!st || steady) {
             // Only the moved rows are touched.  A wave takes only the slots of a
             // batch that hold a moved row for it, so no load is spent on padding;
@@ -1267,7 +1305,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
                         E::unpack(vh[k], x);
                         E::unpack(vm[k], y);
 #pragma unroll
-                        for (int i = 0; i < S::EPL; ++i) acc[i] += (double)y[i] - (double)x[i];
+                        for (int i = 0; i < S::EPL; ++i) acc[k % PARTS][i] += (double)y[i] - (double)x[i];
                     }
                 }
             };
@@ -1313,7 +1351,7 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
                     float x[S::EPL];
                     E::unpack(vh[k], x);
 #pragma unroll
-                    for (int i = 0; i < S::EPL; ++i) acc[i] -= (double)x[i];
+                    for (int i = 0; i < S::EPL; ++i) acc[k % PARTS][i] -= (double)x[i];
                     if (e < n_moves) {
                         const int dst = (int)evl[lds_ix<kSiteEvl>(e, p.evict_cap)];
                         const int src = (int)mvl[lds_ix<kSiteMvl>(e, p.move_cap)];
@@ -1329,7 +1367,8 @@ __global__ void __launch_bounds__(THREADS) step_kernel(const UnitParams p) {
 #pragma unroll
             for (int l = 0; l < kTouchLines; ++l) asm volatile("" ::"v"(tch[i][l]));
         if (st) {
-            const double delta = block_col_total<DT, D, THREADS>(acc, red, red_cap);  // red aliases keys, no longer needed
+            const int listed = steady ? n_moves : n_ev;  // (red aliases keys, no longer needed)
+            const double delta = block_col_total<DT, D>(acc, red, red_cap, listed > S::GROUPS ? PARTS : 1);
             if (threadIdx.x < D) st[threadIdx.x] = (steady ? H.old_sum[threadIdx.x] : H.sum[threadIdx.x]) + delta;
             if (threadIdx.x == 0) st[D] = (double)N;
         }
@@ -1357,9 +1396,9 @@ template <int DT, int D> __global__ void __launch_bounds__(NT) sum_kernel(const 
     const int per = (n + p.splits - 1) / p.splits;
     const int r0 = min(split * per, n), r1 = min(r0 + per, n);
     const int lane = lane_id(), cl = lane % S::LPR, g = wave_id() * S::RPW + lane / S::LPR;
-    double acc[S::EPL];
+    double acc[1][S::EPL];
 #pragma unroll
-    for (int i = 0; i < S::EPL; ++i) acc[i] = 0.0;
+    for (int i = 0; i < S::EPL; ++i) acc[0][i] = 0.0;
     for (int r = r0; r < r1; r += S::GROUPS * kChunks) {
         uint4 w[kChunks];
 #pragma unroll
@@ -1371,7 +1410,7 @@ template <int DT, int D> __global__ void __launch_bounds__(NT) sum_kernel(const 
             float v[S::EPL];
             Elem<DT>::unpack(w[k], v);
 #pragma unroll
-            for (int i = 0; i < S::EPL; ++i) acc[i] += (double)v[i];
+            for (int i = 0; i < S::EPL; ++i) acc[0][i] += (double)v[i];
         }
     }
     const double s = block_col_total<DT, D>(acc, red, NW * D);
@@ -1410,8 +1449,8 @@ __global__ void __launch_bounds__(NT) select_kernel(const UnitParams p) {
     H.hist[threadIdx.x] = 0u;  // NT == kBins
     if (threadIdx.x == 0) H.bc[100] = 0u;
     __syncthreads();
-    uint32_t tch[kTouchIters][kTouchLines];
-    select_and_build(keys, n, N, nullptr, 0, nullptr, 0, keep, H, (p.off_lists - p.off_keys) / 4, nullptr, nullptr,
+    uint32_t tch[1][kTouchLines];
+    select_and_build<NT, 1>(keys, n, N, nullptr, 0, nullptr, 0, keep, H, (p.off_lists - p.off_keys) / 4, nullptr, nullptr,
                      0u, 0, tch);
 }
 
@@ -1645,9 +1684,9 @@ __global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
             sv = vsu[threadIdx.x];
         }
     } else {
-        double ak[S::EPL], av[S::EPL];
+        double ak[1][S::EPL], av[1][S::EPL];
 #pragma unroll
-        for (int i = 0; i < S::EPL; ++i) ak[i] = av[i] = 0.0;
+        for (int i = 0; i < S::EPL; ++i) ak[0][i] = av[0][i] = 0.0;
 #pragma unroll
         for (int j = 0; j < 2 * kGeoRows; ++j) {
             buf[j] = *reinterpret_cast<const uint4 *>(((j & 1) ? vb : kb) + chunk_off(0, j, 0u));
@@ -1663,8 +1702,8 @@ __global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
                 const bool valid = full() || e0 + r * S::GROUPS + g < n;  // selects, not a branch
 #pragma unroll
                 for (int i = 0; i < S::EPL; ++i) {
-                    ak[i] += valid ? (double)x[i] : 0.0;
-                    av[i] += valid ? (double)y[i] : 0.0;
+                    ak[0][i] += valid ? (double)x[i] : 0.0;
+                    av[0][i] += valid ? (double)y[i] : 0.0;
                 }
                 if (e0 < held) {
                     *held_at(e0, 2 * r) = buf[2 * r];
