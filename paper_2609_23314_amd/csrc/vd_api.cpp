@@ -271,7 +271,7 @@ SplitWs split_ws_layout(const vd_cache_desc *d, int64_t units) {
     w.keys_stride = (int64_t(d->capacity) + 3) / 4 * 4;
     w.tot = align16(units * w.keys_stride * 4);
     w.part = w.tot + units * d->head_dim * 8;
-    w.total = w.part + units * max_splits(units) * d->head_dim * 8;
+    w.total = w.part + units * vd::kWaves * d->head_dim * 8;
     return w;
 }
 int64_t step_units(const vd_cache_desc *d) { return int64_t(d->num_seqs) * d->num_layers * d->num_kv_heads; }

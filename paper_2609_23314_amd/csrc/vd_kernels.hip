@@ -705,10 +705,13 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
 // of a unit sums the unit's new rows itself (the same sums in the same order as
 // the whole pass; those few rows come from L2 after the first workgroup) and
 // scores its share of the rest; the keys go through p.ws_keys.  Without a running
-// sum, sum_kernel's partials stand in for a state that covers every row.
-// One GPU, bf16, one workgroup -> split, us: 32 units, d = 128, n = 8193, N = 8192
-// 45.8 -> 19.7 (one unit 40.4 -> 14.9); 36 units, d = 256, n = 5120, N = 4096 73.7 ->
-// 43.6; 32 units, d = 128, n = 8192 without a running sum 154 -> 93.
+// sum, sum_kernel's partials stand in for a state that covers every row.  Every
+// result agrees bit for bit with the whole pass.
+// One GPU, bf16, rows in no cache, one workgroup -> split, us: 32 units, d = 128, n =
+// 8193, N = 8192 44.5 -> 21.2 (one unit 42.0 -> 14.0); 36 units, d = 256, n = 5120,
+// N = 4096 84.3 -> 55.9; without a running sum, d = 128, n = 8192, N = 2048 32 units
+// 94.3 -> 45.6 (Dir 158 -> 95), 64 units 101 -> 66, one unit 89.3 -> 35.9 (30.2 with
+// the sums in as many parts as splits, whose order is not the whole pass's).
 enum : int { kWhole = 0, kRows = 1, kFinish = 2 };
 // (four waves per SIMD: one workgroup of kBlock threads per CU, or two of half as many)
 template <int DT, int D, int VAR, int THREADS, int PART = kWhole>
@@ -782,10 +785,10 @@ __global__ void __launch_bounds__(THREADS, 4) step_kernel(const UnitParams p) {
     double st_col = stp[st ? min((int)threadIdx.x, D) : 0];
     if constexpr (PART == kRows) {
         if (!st) {  // sum_kernel's column sums of all n rows
-            const double *part = p.ws_part + u * p.splits * D + min((int)threadIdx.x, D - 1);
+            const double *part = p.ws_part + u * kWaves * D + min((int)threadIdx.x, D - 1);
             st_col = 0.0;
-#pragma unroll 8
-            for (int i = 0; i < p.splits; ++i) st_col += part[i * D];
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) st_col += part[i * D];
         }
     }
     // what the state covers: the caller's rows but the new ones, or (kRows
@@ -1378,43 +1381,59 @@ __global__ void __launch_bounds__(THREADS, 4) step_kernel(const UnitParams p) {
     }
 }
 
-// Column sums of a unit's n rows in p.splits parts (p.ws_part: [unit][split][D]),
-// for a split pass without a running sum.  Bound by HBM, like the rows' scores.
-template <int DT, int D> __global__ void __launch_bounds__(NT) sum_kernel(const UnitParams p) {
+// Column sums of a unit's n rows for a split pass without a running sum, by
+// kWaves single-wave workgroups: wave w sums the rows that wave w of the whole
+// pass would, in the same order, and leaves its column totals in p.ws_part
+// ([unit][kWaves][D]), which kRows adds in the order of block_col_total.  Bound by
+// HBM, like the rows' scores; a wave keeps kSumChunks rows per lane group in
+// flight.
+constexpr int kSumChunks = 16;
+template <int DT, int D> __global__ void __launch_bounds__(64) sum_kernel(const UnitParams p) {
     using S = Shape<DT, D>;
-    extern __shared__ __align__(16) unsigned char lds[];
-    double *red = reinterpret_cast<double *>(lds);
     int x = blockIdx.x;
-    const int split = x / p.units, ul = x - split * p.units;  // (split-major, as the rows' scores)
+    const int w = x / p.units, ul = x - w * p.units;  // (unit-minor, as the rows' scores)
     x = ul;
     const int head = x % p.num_kv_heads;
     x /= p.num_kv_heads;
     const int layer = x % p.num_layers, sl = x / p.num_layers;
     const int64_t u = (int64_t)p.unit0 + ul;
     const int n = p.nN[2 * sl];
+    if (n <= 0) return;
     const char *vb = p.v + (int64_t)sl * p.s_seq + (int64_t)layer * p.s_layer + (int64_t)head * p.s_head;
-    const int per = (n + p.splits - 1) / p.splits;
-    const int r0 = min(split * per, n), r1 = min(r0 + per, n);
-    const int lane = lane_id(), cl = lane % S::LPR, g = wave_id() * S::RPW + lane / S::LPR;
-    double acc[1][S::EPL];
+    const int lane = lane_id(), cl = lane % S::LPR, g = w * S::RPW + lane / S::LPR;
+    // (cacheable: the rows are read again for their scores)
+    auto load = [&](int e0, int k, uint32_t z) __attribute__((always_inline)) {
+        return *reinterpret_cast<const uint4 *>(vb + row_off(min(e0 + k * S::GROUPS + g, n - 1), p.s_slot, cl) + z);
+    };
+    double acc[S::EPL];
 #pragma unroll
-    for (int i = 0; i < S::EPL; ++i) acc[0][i] = 0.0;
-    for (int r = r0; r < r1; r += S::GROUPS * kChunks) {
-        uint4 w[kChunks];
+    for (int i = 0; i < S::EPL; ++i) acc[i] = 0.0;
+    uint4 buf[kSumChunks];
 #pragma unroll
-        for (int k = 0; k < kChunks; ++k)  // (cacheable: the rows are read again for their scores)
-            w[k] = *reinterpret_cast<const uint4 *>(vb + row_off(min(r + k * S::GROUPS + g, r1 - 1), p.s_slot, cl));
+    for (int k = 0; k < kSumChunks; ++k) buf[k] = load(0, k, 0u);
+    constexpr int kTile = S::GROUPS * kSumChunks;
+    int e0 = 0;
+    for (; e0 + kTile <= n; e0 += kTile) {
 #pragma unroll
-        for (int k = 0; k < kChunks; ++k) {
-            if (r + k * S::GROUPS + g >= r1) continue;
+        for (int k = 0; k < kSumChunks; ++k) {
             float v[S::EPL];
-            Elem<DT>::unpack(w[k], v);
+            Elem<DT>::unpack(buf[k], v);
 #pragma unroll
-            for (int i = 0; i < S::EPL; ++i) acc[0][i] += (double)v[i];
+            for (int i = 0; i < S::EPL; ++i) acc[i] += (double)v[i];
+            buf[k] = load(e0 + kTile, k, zero_after(acc));
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
-    const double s = block_col_total<DT, D>(acc, red, NW * D);
-    if (threadIdx.x < D) p.ws_part[(u * p.splits + split) * D + threadIdx.x] = s;
+#pragma unroll
+    for (int k = 0; k < kSumChunks; ++k) {  // the last tile's rows
+        const bool valid = e0 + k * S::GROUPS + g < n;  // selects, not a branch
+        float v[S::EPL];
+        Elem<DT>::unpack(buf[k], v);
+#pragma unroll
+        for (int i = 0; i < S::EPL; ++i) acc[i] += valid ? (double)v[i] : 0.0;
+    }
+    double *out = p.ws_part + (u * kWaves + w) * D;
+    wave_col_totals<DT, D>(acc, [&](int t, double s) __attribute__((always_inline)) { out[t] = s; });
 }
 
 // Standalone selection: scores (global) -> keep mask.
@@ -2800,7 +2819,7 @@ hipError_t launch_split_step(const UnitParams &p, int num_seqs, int dtype, int h
     void *args[] = {const_cast<UnitParams *>(&p)};
     const dim3 grid(unsigned(p.splits) * unsigned(p.units));
     hipError_t e = hipSuccess;
-    if (!p.running_sum) e = hipLaunchKernel(sum, grid, dim3(NT), args, size_t(NW) * head_dim * 8, stream);
+    if (!p.running_sum) e = hipLaunchKernel(sum, dim3(unsigned(kWaves) * unsigned(p.units)), dim3(64), args, 0, stream);
     if (e == hipSuccess) e = hipLaunchKernel(rows, grid, dim3(NT), args, lds_bytes, stream);
     if (e != hipSuccess) return e;
     return launch(finish, num_seqs, size_t(p.off_stash), stream, p);

@@ -79,7 +79,7 @@ struct UnitParams {
     // split pass: its workspace
     uint32_t *ws_keys;        // [U][keys_stride] the rows' keys
     double *ws_tot;           // [U][D] column sums of all n rows (with a running sum)
-    double *ws_part;          // [U][splits][D] their partial sums (without one)
+    double *ws_part;          // [U][kWaves][D] their partial sums (without one)
     int64_t keys_stride;      // a multiple of 4
     int32_t nN[2 * kMaxSeqsPerLaunch];   // n and N of each sequence of the launch, interleaved
 };

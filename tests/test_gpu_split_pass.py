@@ -1,8 +1,6 @@
 """The pass with several workgroups per unit (``vd_evict_step_split``) against
-the one with a single workgroup, on the same inputs.  With a running sum the
-column sums are added in the same order, so everything agrees bit for bit;
-without one they are added in parts, which moves an fp64 mean by less than n *
-2^-53 of its terms, and an fp32 score by one rounding at most.  Sizes sit where
+the one with a single workgroup, on the same inputs.  The column sums are added
+in the same order, so everything agrees bit for bit.  Sizes sit where
 the split count changes, at shares of less than a row group and of no row, at
 the edges of the staging (all, some and none of the new rows in LDS), at a
 single eviction, at units that do not evict, and at the slot limit."""
@@ -15,6 +13,7 @@ import torch
 from paper_2609_23314_amd import build as lib_build
 from paper_2609_23314_amd import synth, vd
 from paper_2609_23314_amd.driver import EvictingCache
+from test_gpu_half_block import cancelling_rows
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -81,9 +80,29 @@ def test_split_matches_whole(library, dtype, variant, D, shape, ties, state):
         assert lds_word(library) == 0
         runs.append(a)
     ref, got = runs
-    assert torch.allclose(got["scores"], ref["scores"], rtol=0 if state else 2e-7, atol=0)
-    for x in ("k", "v", "pos", "keep") + (("sums",) if state else ()):
+    for x in ("k", "v", "pos", "scores", "keep") + (("sums",) if state else ()):
         assert torch.equal(got[x], ref[x]), x
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("variant", ["l2", "dir"])
+def test_split_sums_in_the_whole_pass_order(dtype, D, variant):
+    """Rows whose sums depend on the order they are added in, without a running sum:
+    the scores of the split pass, of the whole one and of vd_score agree."""
+    R = 768 * 1024 // (D * dtype.itemsize)
+    n = [R + 6, R // 2, 2 * 1024 // dtype.itemsize + 2]
+    k, v = [cancelling_rows((3, 2, 3, R + 6, D), dtype, 5 + i) for i in range(2)]
+    scratch = torch.full((vd.vd_evict_step_split_size(v, k),), 0xFF, dtype=torch.uint8, device=DEV)
+    runs = []
+    for use in (None, scratch):
+        a = [k.clone(), v.clone(), torch.zeros((18, R + 6), device=DEV)]
+        vd.vd_evict_step(*a[:2], n, [m - 100 for m in n], variant, scores_out=a[2], scratch=use)
+        runs.append(a)
+    for x, y in zip(*runs):
+        assert torch.equal(x, y)
+    alone = vd.vd_score(v, n, variant, scores=torch.zeros((18, R + 6), device=DEV))[0]
+    assert torch.equal(alone, runs[0][2])
 
 
 def test_scratch_is_checked():
