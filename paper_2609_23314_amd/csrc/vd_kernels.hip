@@ -783,7 +783,7 @@ __global__ void __launch_bounds__(THREADS, 4) step_kernel(const UnitParams p) {
     const double *stp = st ? st : reinterpret_cast<const double *>(vb);
     const double craw = stp[st ? D : 0];
     double st_col = stp[st ? min((int)threadIdx.x, D) : 0];
-    if constexpr (PART == kRows) {
+    if constexpr (PART == kRows && (VAR == kL2 || VAR == kDir)) {  // (the norms need no mean)
         if (!st) {  // sum_kernel's column sums of all n rows
             const double *part = p.ws_part + u * kWaves * D + min((int)threadIdx.x, D - 1);
             st_col = 0.0;
@@ -1397,8 +1397,8 @@ template <int DT, int D> __global__ void __launch_bounds__(64) sum_kernel(const 
     x /= p.num_kv_heads;
     const int layer = x % p.num_layers, sl = x / p.num_layers;
     const int64_t u = (int64_t)p.unit0 + ul;
-    const int n = p.nN[2 * sl];
-    if (n <= 0) return;
+    const int n = p.nN[2 * sl], N = p.nN[2 * sl + 1];
+    if (n <= 0 || (n <= N && !p.scores)) return;  // a unit without scores needs no mean
     const char *vb = p.v + (int64_t)sl * p.s_seq + (int64_t)layer * p.s_layer + (int64_t)head * p.s_head;
     const int lane = lane_id(), cl = lane % S::LPR, g = w * S::RPW + lane / S::LPR;
     // (cacheable: the rows are read again for their scores)
@@ -2814,12 +2814,13 @@ hipError_t launch_split_step(const UnitParams &p, int num_seqs, int dtype, int h
                              size_t lds_bytes, hipStream_t stream) {
     void *rows = step_kernel_for<kBlock, kRows>(dtype, head_dim, variant);
     void *finish = step_kernel_for<kBlock, kFinish>(dtype, head_dim, variant);
+    const bool mean = !p.running_sum && variant != 2 && variant != 5;  // (not for the norms)
     void *sum = dtype == 0 ? sum_kernel_for<0>(head_dim) : sum_kernel_for<1>(head_dim);
     if (!rows || !finish || !sum) return hipErrorInvalidDeviceFunction;
     void *args[] = {const_cast<UnitParams *>(&p)};
     const dim3 grid(unsigned(p.splits) * unsigned(p.units));
     hipError_t e = hipSuccess;
-    if (!p.running_sum) e = hipLaunchKernel(sum, dim3(unsigned(kWaves) * unsigned(p.units)), dim3(64), args, 0, stream);
+    if (mean) e = hipLaunchKernel(sum, dim3(unsigned(kWaves) * unsigned(p.units)), dim3(64), args, 0, stream);
     if (e == hipSuccess) e = hipLaunchKernel(rows, grid, dim3(NT), args, lds_bytes, stream);
     if (e != hipSuccess) return e;
     return launch(finish, num_seqs, size_t(p.off_stash), stream, p);

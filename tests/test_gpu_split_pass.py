@@ -105,6 +105,25 @@ def test_split_sums_in_the_whole_pass_order(dtype, D, variant):
     assert torch.equal(alone, runs[0][2])
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("variant,scores,summed", [("norm", True, []), ("key_norm", False, []), ("l2", False, [0]),
+                                                   ("l2", True, [0, 1]), ("dir", False, [0])])
+def test_columns_are_summed_only_for_a_mean(dtype, variant, scores, summed):
+    """Without a running sum: the norms need no column sums, nor does a unit that
+    neither evicts nor reports scores (their place in the scratch is left alone)."""
+    D, L, H = 128, 1, 3
+    n = [768 * 1024 // (D * dtype.itemsize) + 40, 300, 0]
+    C, U = n[0], 3 * L * H
+    k, v = [synth.random_rows((3, L, H, C, D), dtype, 31 + i, DEV) for i in range(2)]
+    scratch = torch.full((vd.vd_evict_step_split_size(v, k),), 0xFF, dtype=torch.uint8, device=DEV)
+    part = U * ((C + 3) // 4 * 4) * 4 + U * D * 8
+    out = torch.zeros((U, C), device=DEV) if scores else None
+    vd.vd_evict_step(k, v, n, [n[0] - 40, 300, 5], variant, scores_out=out, scratch=scratch)
+    sums = scratch[part:].view(3, -1)
+    assert sums.numel() == U * 16 * D * 8
+    assert [s for s in range(3) if bool((sums[s] != 0xFF).any())] == summed
+
+
 def test_scratch_is_checked():
     k, v = torch.zeros((2, 1, 1, 2, 4096, 128), dtype=torch.bfloat16, device=DEV)  # 1 MB a unit
     size = vd.vd_evict_step_split_size(v, k)
