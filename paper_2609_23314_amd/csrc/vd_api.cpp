@@ -472,13 +472,17 @@ vd_status vd_geometry(const vd_cache_desc *desc, const int32_t *n_valid, const d
         p.v_sum = v_sum;
         p.off_keys = int32_t(sizeof(vd::LdsHead));
         p.off_lists = int32_t(p.off_keys + red_bytes);
-        // the first bf16 rows of K and V stay in LDS from one stream to the other, in whole tiles
+        // The first bf16 rows of K and V stay in LDS from one stream to the other, in
+        // whole tiles, where a unit has more than two of them: with fewer, what the LDS
+        // takes keeps the next unit's workgroup from starting beside the last waves of
+        // this one (not held and held, us: 1024 units of 200 x 128 52.2 and 56.8, of 100 x
+        // 64 37.7 and 42.8, of 400 x 128 80.0 and 77.0, of 200 x 256 89.5 and 84.6).
         const int64_t tile_bytes = 2 * vd::kGeoRows * int64_t(vd::kBlock) * 16;
         const int64_t tile_rows = tile_bytes / (2 * int64_t(desc->head_dim) * elem_bytes(desc->dtype));
         int nmax = 0;
         for (int i = 0; i < ns; ++i) nmax = std::max(nmax, p.nN[2 * i]);
         p.off_stash = int32_t(p.off_lists + ctr_bytes);
-        const int64_t tiles = k_sum || desc->dtype != VD_DTYPE_BF16 ? 0
+        const int64_t tiles = k_sum || desc->dtype != VD_DTYPE_BF16 || nmax <= 2 * tile_rows ? 0
                                               : std::min<int64_t>((vd::kLdsBytes - p.off_stash) / tile_bytes,
                                                                   (nmax + tile_rows - 1) / tile_rows);
         p.stash_rows = int32_t(tiles * tile_rows);

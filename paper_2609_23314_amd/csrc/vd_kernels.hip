@@ -1626,13 +1626,17 @@ template <int DT> __device__ __forceinline__ float row_elem(const char *row, int
 // lo), so that its error stays at fp32 rounding of the distance however far
 // the centroid lies from the origin; every sum over rows is fp64, in a fixed
 // order.  With two streams the first keeps the rows cacheable, and as many whole
-// tiles of bf16 rows as LDS has room for (128 KB) stay there; the second stream
+// tiles of bf16 rows as LDS has room for (128 KB, 64 KB at d = 256) stay there; the second stream
 // reads the others once more, in reverse order and without retention.  Bound by
 // those two reads (256 units of 2560 rows, d = 128: 671 MB, 103.4 us at first, 100.5
 // with the held rows, 98 with four distances at a time; four rows per lane group in
 // flight instead of two took 119).
+// (five and eight waves per SIMD: two workgroups of fp32 rows per CU, and one of bf16
+// rows with room for the next one's waves beside its last ones: 1024 units of 100 x 64
+// with their sums 28.0 us, 31.5 at the 104 registers that K's and V's fp64 conversions
+// side by side take)
 template <int DT, int D>
-__global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
+__global__ void __launch_bounds__(NT, DT == 0 ? 5 : 8) geometry_kernel(const UnitParams p) {
     using S = Shape<DT, D>;
     using E = Elem<DT>;
     constexpr int kTile = S::GROUPS * kGeoRows;  // rows per tile
@@ -1715,15 +1719,15 @@ __global__ void __launch_bounds__(NT) geometry_kernel(const UnitParams p) {
         auto sum_tile = [&](int e0, auto full) __attribute__((always_inline)) {
 #pragma unroll
             for (int r = 0; r < kGeoRows; ++r) {
+                const bool valid = full() || e0 + r * S::GROUPS + g < n;  // selects, not a branch
                 float x[S::EPL], y[S::EPL];
                 E::unpack(buf[2 * r], x);
-                E::unpack(buf[2 * r + 1], y);
-                const bool valid = full() || e0 + r * S::GROUPS + g < n;  // selects, not a branch
 #pragma unroll
-                for (int i = 0; i < S::EPL; ++i) {
-                    ak[0][i] += valid ? (double)x[i] : 0.0;
-                    av[0][i] += valid ? (double)y[i] : 0.0;
-                }
+                for (int i = 0; i < S::EPL; ++i) ak[0][i] += valid ? (double)x[i] : 0.0;
+                __builtin_amdgcn_sched_barrier(0);
+                E::unpack(buf[2 * r + 1], y);
+#pragma unroll
+                for (int i = 0; i < S::EPL; ++i) av[0][i] += valid ? (double)y[i] : 0.0;
                 if (e0 < held) {
                     *held_at(e0, 2 * r) = buf[2 * r];
                     *held_at(e0, 2 * r + 1) = buf[2 * r + 1];

@@ -103,3 +103,16 @@ def test_decode_split_keeps_three_workgroups_per_cu(kernels):
         body = _kernel_body(text, part)
         assert "v_mfma_f32_4x4x1_16b_f32" in body, part
         assert "v_accvgpr" not in body, part
+
+
+@pytest.mark.parametrize("kernel,limit", [("step_kernel", 128), ("geometry_kernelILi0", 96), ("geometry_kernelILi1", 64)])
+def test_workgroups_per_cu(kernels, kernel, limit):
+    """Registers that the workgroups per CU rely on (512 per SIMD lane, in steps of
+    8): the pass, 128 for one workgroup of 1024 threads or two of 512; the geometry,
+    64 for two workgroups of fp32 rows and 96 for one of bf16 rows and the first
+    waves of the next."""
+    text, _, _ = kernels
+    regs = dict(re.findall(r"\.amdhsa_kernel (\S*" + kernel + r"\S*)\n(?:.*\n)*?\s*\.amdhsa_next_free_vgpr (\d+)", text))
+    assert len(regs) >= 3, regs
+    over = {k: int(v) for k, v in regs.items() if int(v) > limit}
+    assert not over, over
