@@ -2429,11 +2429,11 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
 // at a time, all their words read before any is used (one memory round trip
 // per batch; up to 5120 rows are one batch); the caller has read the first batch.
 constexpr int kRowsAtOnce = 5;
-template <int G, int T> struct CaoteRows {
-    float x[kRowsAtOnce][G + 1];
+template <int G, int T, int R = kRowsAtOnce> struct CaoteRows {
+    float x[R][G + 1];
     __device__ __forceinline__ void load(const float *rows, int64_t plane, int j0, int n) {
 #pragma unroll
-        for (int r = 0; r < kRowsAtOnce; ++r) {
+        for (int r = 0; r < R; ++r) {
             const int j = min(j0 + r * T, n - 1);  // past the end: row n - 1 again, unused
 #pragma unroll
             for (int g = 0; g <= G; ++g) x[r][g] = rows[g * plane + j];
@@ -2449,10 +2449,10 @@ template <int G, int T> struct CaoteRows {
             inv[g] = 1.f / Lw[g];
         }
         unsigned long long best = ~0ull;
-        for (int j0 = threadIdx.x; j0 < n; j0 += kRowsAtOnce * T) {
+        for (int j0 = threadIdx.x; j0 < n; j0 += R * T) {
             if (j0 != (int)threadIdx.x) load(rows, plane, j0, n);
 #pragma unroll
-            for (int r = 0; r < kRowsAtOnce; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const int j = j0 + r * T;
                 float a = 0.f, rest = 0.f;
 #pragma unroll
@@ -2658,13 +2658,20 @@ __global__ void __launch_bounds__(kCombineThreads) attn_combine_kernel(const Uni
         evict_row<DT, D>(p, u, kb, vb, st, cnt, old, kl, vl, pl, xj, c, j, n, N);
 }
 
-// The same for at most kMergeBatch splits and ValueDiff: every thread reads its
-// columns' partials and the head's maxima and sums of all splits at once and
-// needs nothing from the others, so the block waits for memory twice (the
-// argmin words, then the evicted row) and for no barrier.  decode_b16's layer
-// call (128 units, six splits) takes 5.1 us here, 6.3 us above.
-template <int DT, int D, int G>
+// The same for at most kMergeBatch splits by kAttnThreads: every thread reads its
+// columns' partials and the head's maxima and sums of all splits at once, so that
+// with ValueDiff it needs nothing from the others: the block waits for memory
+// twice (the argmin words, then the evicted row) and for no barrier.  decode_b16's
+// layer call (128 units, six splits) takes 5.1 us here, 6.3 us above.  FastCAOTE
+// comes here with more units than CUs, which fill the chip without 1024 threads
+// each, nine rows per thread at a time (us a call, the kernel above in brackets):
+// 1024 units of 300 rows, d = 64, G = 2 26.2 [37.0], 512 of 1000 rows 35.9 [41.1], of
+// 4096 112.7 [115.8] (five rows at a time 25.1, 35.3 and 112.6, but up to 3 % more
+// where that is four batches; seventeen 30 in the first).
+template <int DT, int D, int G, bool CAOTE>
 __global__ void __launch_bounds__(kAttnThreads) attn_combine_few_kernel(const UnitParams p) {
+    __shared__ float mg[G], lg[G];
+    __shared__ unsigned long long wbest[kAttnWaves];
     using A = AttnShape<DT, D>;
     constexpr int EPL = A::EPL, LPR = A::LPR;
     constexpr int kOut = (G * D + kAttnThreads - 1) / kAttnThreads;  // outputs per thread
@@ -2686,6 +2693,28 @@ __global__ void __launch_bounds__(kAttnThreads) attn_combine_few_kernel(const Un
     const bool ev = c >= 0 && c < LPR;
     const int ce = ev ? c : 0;
     const int last = n > 0 ? n - 1 : 0;
+    const float *ml = p.ws_ml + u * S * G * 2;
+    CaoteRows<G, kAttnThreads, 9> cr;
+    const float *rows = p.ws_rows + u * p.capacity * (G + 1);
+    if constexpr (CAOTE) {
+        cr.load(rows, p.capacity, threadIdx.x, max(n, 1));
+        if (threadIdx.x < G) {
+            const int g = threadIdx.x;
+            float m[kMergeBatch], l[kMergeBatch], top = kNoLogit, den = 0.f;
+#pragma unroll
+            for (int i = 0; i < kMergeBatch; ++i) {
+                const int s = i < S ? i : 0;
+                m[i] = ml[(s * G + g) * 2];
+                l[i] = ml[(s * G + g) * 2 + 1];
+            }
+#pragma unroll
+            for (int i = 0; i < kMergeBatch; ++i) top = fmaxf(top, m[i]);
+#pragma unroll
+            for (int i = 0; i < kMergeBatch; ++i) den = i < S ? fmaf(l[i], __builtin_amdgcn_exp2f(m[i] - top), den) : den;
+            mg[g] = top;
+            lg[g] = den;
+        }
+    }
     const double cnt = st[D];
     double old[EPL];
 #pragma unroll
@@ -2699,11 +2728,22 @@ __global__ void __launch_bounds__(kAttnThreads) attn_combine_few_kernel(const Un
     int64_t pix = has_pos ? u * p.capacity + N : 0;
     asm volatile("" : "+v"(pix));
     const int32_t pl = pbase[pix];
-    const unsigned long long lowest = wave_min_u64(p.ws_amin[u * S + min(lane_id(), S - 1)]);
+    unsigned long long lowest = ~0ull;
+    if constexpr (CAOTE) {
+        if (evict) {  // uniform branch
+            __syncthreads();
+            lowest = wave_min_u64(cr.lowest(rows, p.capacity, n, mg, lg));
+            if (lane_id() == 0) wbest[wave_id()] = lowest;
+            __syncthreads();
+            lowest = wbest[min(lane_id(), kAttnWaves - 1)];
+        }
+    } else {
+        lowest = p.ws_amin[u * S + min(lane_id(), S - 1)];
+    }
+    lowest = wave_min_u64(lowest);
     const int j = evict ? (int)~(uint32_t)lowest : -1;
     const uint4 xj = load_stream(vb, row_off(j >= 0 ? j : 0, ss32, ce));  // used after the outputs
     float *orow = p.attn_out + (((int64_t)sl * p.num_layers + layer) * p.num_kv_heads + head) * G * D;
-    const float *ml = p.ws_ml + u * S * G * 2;
     const float *pa = p.ws_acc + u * S * G * D;
 #pragma unroll
     for (int o = 0; o < kOut; ++o) {
@@ -2734,28 +2774,26 @@ __global__ void __launch_bounds__(kAttnThreads) attn_combine_few_kernel(const Un
         evict_row<DT, D>(p, u, kb, vb, st, cnt, old, kl, vl, pl, xj, c, j, n, N);
 }
 
-// Kernels of the fused decode step; the combine for `splits` splits.
-template <int DT, int D, int G> void *attn_kernel_for(bool caote, bool combine, int splits) {
-    if (caote)
-        return combine ? reinterpret_cast<void *>(&attn_combine_kernel<DT, D, G, true>)
-                       : reinterpret_cast<void *>(&attn_split_kernel<DT, D, G, true>);
-    if (!combine) return reinterpret_cast<void *>(&attn_split_kernel<DT, D, G, false>);
-    return splits <= kMergeBatch ? reinterpret_cast<void *>(&attn_combine_few_kernel<DT, D, G>)
-                                 : reinterpret_cast<void *>(&attn_combine_kernel<DT, D, G, false>);
+// Kernels of the fused decode step.
+enum AttnKernel { kAttnSplit, kAttnCombine, kAttnCombineFew };
+template <int DT, int D, int G, bool CAOTE> void *attn_kernel_for(AttnKernel which) {
+    return which == kAttnSplit     ? reinterpret_cast<void *>(&attn_split_kernel<DT, D, G, CAOTE>)
+           : which == kAttnCombine ? reinterpret_cast<void *>(&attn_combine_kernel<DT, D, G, CAOTE>)
+                                   : reinterpret_cast<void *>(&attn_combine_few_kernel<DT, D, G, CAOTE>);
 }
-template <int DT, int D> void *attn_kernel_for(int group, bool caote, bool combine, int splits) {
+template <int DT, int D> void *attn_kernel_for(int group, bool caote, AttnKernel which) {
     switch (group) {
-        case 1: return attn_kernel_for<DT, D, 1>(caote, combine, splits);
-        case 2: return attn_kernel_for<DT, D, 2>(caote, combine, splits);
-        case 4: return attn_kernel_for<DT, D, 4>(caote, combine, splits);
+        case 1: return caote ? attn_kernel_for<DT, D, 1, true>(which) : attn_kernel_for<DT, D, 1, false>(which);
+        case 2: return caote ? attn_kernel_for<DT, D, 2, true>(which) : attn_kernel_for<DT, D, 2, false>(which);
+        case 4: return caote ? attn_kernel_for<DT, D, 4, true>(which) : attn_kernel_for<DT, D, 4, false>(which);
     }
     return nullptr;
 }
-template <int DT> void *attn_kernel_for(int head_dim, int group, bool caote, bool combine, int splits) {
+template <int DT> void *attn_kernel_for(int head_dim, int group, bool caote, AttnKernel which) {
     switch (head_dim) {
-        case 64: return attn_kernel_for<DT, 64>(group, caote, combine, splits);
-        case 128: return attn_kernel_for<DT, 128>(group, caote, combine, splits);
-        case 256: return attn_kernel_for<DT, 256>(group, caote, combine, splits);
+        case 64: return attn_kernel_for<DT, 64>(group, caote, which);
+        case 128: return attn_kernel_for<DT, 128>(group, caote, which);
+        case 256: return attn_kernel_for<DT, 256>(group, caote, which);
     }
     return nullptr;
 }
@@ -2905,17 +2943,18 @@ hipError_t launch_geometry(const UnitParams &p, int num_seqs, int dtype, int hea
 
 hipError_t launch_attn(const UnitParams &p, int num_seqs, int dtype, int head_dim, int group,
                        bool caote, size_t split_lds, hipStream_t stream) {
-    void *fs = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, false, p.splits)
-                          : attn_kernel_for<1>(head_dim, group, caote, false, p.splits);
-    void *fc = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, true, p.splits)
-                          : attn_kernel_for<1>(head_dim, group, caote, true, p.splits);
+    const bool few = p.splits <= kMergeBatch && (!caote || int64_t(num_seqs) * p.num_layers * p.num_kv_heads > kCus);
+    const AttnKernel combine = few ? kAttnCombineFew : kAttnCombine;
+    void *fs = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, kAttnSplit)
+                          : attn_kernel_for<1>(head_dim, group, caote, kAttnSplit);
+    void *fc = dtype == 0 ? attn_kernel_for<0>(head_dim, group, caote, combine)
+                          : attn_kernel_for<1>(head_dim, group, caote, combine);
     if (!fs || !fc || p.splits > kMaxSplits) return hipErrorInvalidDeviceFunction;
     void *args[] = {const_cast<UnitParams *>(&p)};
     const unsigned sz = (unsigned)(num_seqs * p.num_layers);
     hipError_t e = hipLaunchKernel(fs, dim3(p.splits, p.num_kv_heads, sz), dim3(kAttnThreads), args,
                                    split_lds, stream);
     if (e != hipSuccess) return e;
-    const bool few = !caote && p.splits <= kMergeBatch;
     return hipLaunchKernel(fc, dim3(p.num_kv_heads, sz), dim3(few ? kAttnThreads : kCombineThreads), args, 0, stream);
 }
 

@@ -235,6 +235,23 @@ def test_fastcaote_decode_step_matches_oracle(orc, dt, D, G):
     assert ties <= 1, ties
 
 
+@pytest.mark.parametrize("dt,D", [("bf16", 64), ("f32", 64), ("bf16", 256)])
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_fastcaote_many_units(orc, dt, D, G):
+    """More units than compute units merge their splits by 256 threads each, which
+    take 2304 rows at a time: units at and beside that many, with an eviction or
+    without, and the shortest."""
+    n = [2305, 2304, 2306, 256, 257, 2, 1, 0, 1537] * (29 if D == 64 else 2)
+    L, H = (1, 1) if D == 64 else (3, 5)
+    N = [max(1, x - (s % 5 != 4)) for s, x in enumerate(n)]
+    n = n if D == 64 else [min(x, 700) for x in n]
+    N = N if D == 64 else [max(1, min(x, 699)) for x in N]
+    sample = [s * L * H + s % (L * H) for s in range(18)]
+    ties, *_ = run_case(orc, len(n), L, H, G, max(n) + 1, D, DTYPES[dt], n, N, seed=640 + D + G, sample=sample,
+                        variant="fastcaote")
+    assert ties <= 1, ties
+
+
 def test_fastcaote_uniform_attention_evicts_like_valuediff(orc):
     """Zero queries weigh every row 1/n, so FastCAOTE's scores are the L2
     scores / (n - 1) and it evicts the row ValueDiff evicts (App. A: the
