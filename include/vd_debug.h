@@ -27,6 +27,13 @@ extern "C" {
  * only. */
 vd_status vd_debug_take_error_word(uint32_t *word);
 
+/* How the calling thread's last pass (vd_score, vd_evict_step or
+ * vd_evict_step_split) was launched: threads per workgroup, and workgroups
+ * that share a unit's rows (0: one does the whole pass).  Both 0 before the
+ * first; of a call in several launches, the last one's.  VD_ERR_INVALID_ARG
+ * for a null pointer.  Exported by libvd_debug.so only. */
+vd_status vd_debug_last_pass(int32_t *threads, int32_t *splits);
+
 #ifdef __cplusplus
 }
 #endif

@@ -276,6 +276,18 @@ SplitWs split_ws_layout(const vd_cache_desc *d, int64_t units) {
 }
 int64_t step_units(const vd_cache_desc *d) { return int64_t(d->num_seqs) * d->num_layers * d->num_kv_heads; }
 
+#if VD_DEBUG
+thread_local int32_t last_pass[2];  // threads per workgroup and splits of this thread's last pass
+#endif
+vd_status launch_pass(const UnitParams &p, int ns, const vd_cache_desc *d, vd_variant variant, size_t lds,
+                      hipStream_t stream) {
+#if VD_DEBUG
+    last_pass[0] = p.threads;
+    last_pass[1] = p.splits;
+#endif
+    return launched(vd::launch_step(p, ns, d->dtype, d->head_dim, variant, lds, stream));
+}
+
 // The pass over a validated call; scratch (or null): split_ws_layout's bytes.
 vd_status evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const int32_t *budget,
                      vd_variant variant, double *running_sum, int32_t *pos, float *scores_out,
@@ -313,7 +325,7 @@ vd_status evict_step(const vd_cache_desc *desc, const int32_t *n_valid, const in
             if ((st = plan_step(desc, p, ns, false, running_sum != nullptr, scores_out != nullptr, lds)) != VD_OK)
                 return st;
         }
-        st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds, stream));
+        st = launch_pass(p, ns, desc, variant, lds, stream);
         if (st != VD_OK) return st;
     }
     return VD_OK;
@@ -356,8 +368,7 @@ vd_status vd_score(const vd_cache_desc *desc, const int32_t *n_valid, vd_variant
         p.mean_out = mean_out;
         size_t lds = 0;
         if ((st = plan_step(desc, p, ns, true, false, true, lds)) != VD_OK) return st;
-        st = launched(vd::launch_step(p, ns, desc->dtype, desc->head_dim, variant, lds,
-                                      reinterpret_cast<hipStream_t>(stream)));
+        st = launch_pass(p, ns, desc, variant, lds, reinterpret_cast<hipStream_t>(stream));
         if (st != VD_OK) return st;
     }
     return VD_OK;
@@ -553,6 +564,13 @@ vd_status vd_debug_take_error_word(uint32_t *word) {
     unsigned int w = 0u;
     if (vd::debug_take_error_word(&w) != hipSuccess) return VD_ERR_HIP;
     *word = w;
+    return VD_OK;
+}
+
+vd_status vd_debug_last_pass(int32_t *threads, int32_t *splits) {
+    if (!threads || !splits) return VD_ERR_INVALID_ARG;
+    *threads = last_pass[0];
+    *splits = last_pass[1];
     return VD_OK;
 }
 #endif

@@ -34,13 +34,15 @@ def test_library_exports_every_declared_symbol():
     for name in declared_functions():
         assert hasattr(lib, name), name
     assert not hasattr(lib, "vd_debug_take_error_word")   # the release build has no checks
+    assert not hasattr(lib, "vd_debug_last_pass")
 
 
 def test_debug_library_exports_every_declared_symbol():
     from paper_2609_23314_amd import build as lib_build
     lib = ctypes.CDLL(lib_build.DEBUG_LIB)
-    for name in declared_functions() + ["vd_debug_take_error_word"]:
+    for name in declared_functions() + ["vd_debug_take_error_word", "vd_debug_last_pass"]:
         assert hasattr(lib, name), name
+    assert lib.vd_debug_last_pass(None, None) == vd.VD_ERR_INVALID_ARG
     lib.vd_debug_take_error_word.argtypes = [ctypes.c_void_p]
     assert lib.vd_debug_take_error_word(None) == vd.VD_ERR_INVALID_ARG
 

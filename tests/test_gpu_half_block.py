@@ -35,10 +35,18 @@ def library(request):
     vd._lib, vd.LIB_PATH = saved
 
 
+def last_pass(library):
+    """Threads per workgroup and splits of this thread's last pass (debug build)."""
+    threads, splits = ctypes.c_int32(-1), ctypes.c_int32(-1)
+    assert library.vd_debug_last_pass(ctypes.byref(threads), ctypes.byref(splits)) == vd.VD_OK
+    return threads.value, splits.value
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("variant", ["l2", "dir", "norm", "key_norm"])
 @pytest.mark.parametrize("D,n,N,ties", [(D, n, N, False) for D in (64, 128, 256) for n, N in SIZES] +
-                         [(128, *SIZES[3], True), (64, [2300, 2100, 2050], [1300, 1500, 2050], False)])
+                         [(128, *SIZES[3], True), (64, [2300, 2100, 2050], [1300, 1500, 2050], False),
+                          (64, [2300, 2100, 2050], [2200, 2060, 2050], False), (256, [40, 2, 1], [3, 1, 1], False)])
 def test_half_block_matches_full(library, dtype, D, variant, n, N, ties):
     C, U = max(n) + 3, S * L * H
     k, v = [synth.random_rows((S, L, H, C, D), dtype, 91 + i, DEV) for i in range(2)]
@@ -59,11 +67,15 @@ def test_half_block_matches_full(library, dtype, D, variant, n, N, ties):
     ref = {a: x.clone() for a, x in got.items()}
     vd.vd_evict_step(k, v, n, N, variant, running_sum=sums.view(U, -1), pos=pos, scores_out=got["scores"],
                      keep_out=got["keep"])
+    if library is not None:  # fp32 rows that half the LDS cannot stage take the full workgroup here too
+        full = dtype == torch.float32 and ((D == 256 and n[0] == 67) or (D == 64 and N[0] == 1300))
+        assert last_pass(library) == (1024 if full else 512, 0)
     for s in range(S):
         u = slice(s * L * H, (s + 1) * L * H)
         vd.vd_evict_step(one[0][s:s + 1], one[1][s:s + 1], n[s:s + 1], N[s:s + 1], variant,
                          running_sum=one[2][s].view(L * H, -1), pos=one[3][u], scores_out=ref["scores"][u],
                          keep_out=ref["keep"][u])
+        assert library is None or last_pass(library) == (1024, 0)
     for a, b in zip((k, v, pos), (one[0], one[1], one[3])):
         assert torch.equal(a, b)
     assert torch.equal(got["keep"], ref["keep"]) and torch.equal(got["scores"], ref["scores"])

@@ -13,7 +13,7 @@ import torch
 from paper_2609_23314_amd import build as lib_build
 from paper_2609_23314_amd import synth, vd
 from paper_2609_23314_amd.driver import EvictingCache
-from test_gpu_half_block import cancelling_rows
+from test_gpu_half_block import cancelling_rows, last_pass
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -78,6 +78,9 @@ def test_split_matches_whole(library, dtype, variant, D, shape, ties, state):
         vd.vd_evict_step(a["k"], a["v"], n, N, variant, running_sum=a["sums"], pos=a["pos"], scores_out=a["scores"],
                          keep_out=a["keep"], scratch=use)
         assert lds_word(library) == 0
+        if library is not None:  # each of the 256 compute units' share of the units, 64 at most and 64 KB of rows
+            most = min(64, 256 // U, max(a for a, b in zip(n, N) if a > b) * D * dtype.itemsize // 65536)
+            assert last_pass(library) == (1024, 0 if use is None else most)
         runs.append(a)
     ref, got = runs
     for x in ("k", "v", "pos", "scores", "keep") + (("sums",) if state else ()):
