@@ -19,6 +19,7 @@ hipError_t launch_select(const UnitParams &, int, size_t, hipStream_t) { return 
 hipError_t launch_compact(const UnitParams &, int, int, int, size_t, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_attn(const UnitParams &, int, int, int, int, bool, size_t, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_geometry(const UnitParams &, int, int, int, size_t, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_append(const AppendParams &, int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_stream_read(const void *, size_t, uint32_t *, hipStream_t) { return hipErrorNoDevice; }
 hipError_t scratch_memory(hipStream_t, void **) { return hipErrorNoDevice; }
 }  // namespace vd
@@ -72,6 +73,38 @@ int main() {
                     EXPECT(vd_evict_step(&d, n.data(), N.data(), vd_variant(var), db, i32, f, u8, nullptr,
                                          0, nullptr) == VD_ERR_HIP);
                 }
+                // the pass with scratch: none needed with many units or short ones
+                const size_t split = vd_evict_step_split_size(&d);
+                EXPECT((split > 0) == (S <= 16 && int64_t(C) * D * (dtype ? 4 : 2) >= 768 * 1024));
+                for (int var = 0; var <= 5; ++var)
+                    EXPECT(vd_evict_step_split(&d, n.data(), N.data(), vd_variant(var), var & 1 ? db : nullptr, i32, f,
+                                               u8, dev, split, nullptr) == VD_ERR_HIP);
+                EXPECT(vd_evict_step_split(&d, n.data(), N.data(), VD_SCORE_L2, db, i32, f, u8, nullptr, 0, nullptr) ==
+                       (split ? VD_ERR_WORKSPACE : VD_ERR_HIP));
+                if (split) {
+                    EXPECT(vd_evict_step_split(&d, n.data(), N.data(), VD_SCORE_L2, db, i32, f, u8, dev, split - 1,
+                                               nullptr) == VD_ERR_WORKSPACE);
+                    EXPECT(vd_evict_step_split(&d, n.data(), N.data(), VD_SCORE_L2, db, i32, f, u8,
+                                               static_cast<char *>(dev) + 8, split, nullptr) == VD_ERR_WORKSPACE);
+                }
+                // appends: the last sequence's first and last slots, rows in any order of layers and heads
+                const int64_t rows_first[3] = {2 * 40 * D, 40 * D, D}, heads_first[3] = {D, 2 * D, 4 * D};
+                const int64_t odd[3] = {2 * 40 * D, 40 * D, D + 1}, far[3] = {INT64_MAX, 0, 0}, back[3] = {-D, 0, D};
+                void *rows = reinterpret_cast<void *>(0x7d0000000000ull);
+                for (int32_t t : {1, 40})
+                    for (int32_t at : {0, C - 40})
+                        EXPECT(vd_append(&d, S - 1, at, t, rows, rows_first, rows, heads_first, i32, 7, nullptr) ==
+                               VD_ERR_HIP);
+                for (const int64_t *bad : {odd, far, back})
+                    EXPECT(vd_append(&d, 0, 0, 40, rows, bad, rows, rows_first, i32, 0, nullptr) == VD_ERR_INVALID_ARG);
+                EXPECT(vd_append(&d, 0, C - 39, 40, rows, rows_first, rows, rows_first, i32, 0, nullptr) ==
+                       VD_ERR_INVALID_ARG);
+                EXPECT(vd_append(&d, 0, 0, 40, d.v, rows_first, rows, rows_first, i32, 0, nullptr) ==
+                       VD_ERR_INVALID_ARG);
+                EXPECT(vd_append(&d, 0, 0, 40, rows, rows_first, rows, rows_first, i32, INT32_MAX - 39, nullptr) ==
+                       VD_ERR_INVALID_ARG);
+                EXPECT(vd_append(&d, S, 0, 1, rows, rows_first, rows, rows_first, i32, 0, nullptr) ==
+                       VD_ERR_INVALID_ARG);
                 EXPECT(vd_select_topn(&d, f, n.data(), N.data(), u8, nullptr) == VD_ERR_HIP);
                 EXPECT(vd_compact(&d, u8, n.data(), N.data(), i32, nullptr) != VD_ERR_INVALID_ARG);
                 EXPECT(vd_geometry(&d, n.data(), nullptr, nullptr, db, nullptr) == VD_ERR_HIP);

@@ -38,6 +38,7 @@ def test_host_abi_under_sanitizers(tmp_path):
     _run(["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE,
           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2609_23314_amd", "csrc"),
           "-o", exe, os.path.join(HERE, "sanitize", "host_main.cpp"),
-          os.path.join(ROOT, "paper_2609_23314_amd", "csrc", "vd_api.cpp")])
+          os.path.join(ROOT, "paper_2609_23314_amd", "csrc", "vd_api.cpp"),
+          os.path.join(ROOT, "paper_2609_23314_amd", "csrc", "vd_append.cpp")])
     out = _run([exe], env={**os.environ, "ASAN_OPTIONS": "detect_leaks=1"}, timeout=300)
     assert "host sanitizer run ok" in out
