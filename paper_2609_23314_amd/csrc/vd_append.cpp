@@ -27,6 +27,10 @@ extern "C" vd_status vd_append(const vd_cache_desc *desc, int32_t seq, int32_t n
     // units that share memory would be written at once
     if ((L > 1 && desc->stride_layer == 0) || (H > 1 && desc->stride_head == 0)) return VD_ERR_INVALID_ARG;
     if (units > INT32_MAX / 2) return VD_ERR_UNSUPPORTED;
+    // byte offsets and the extents compared below stay far from 64 bits
+    if (desc->stride_seq > (int64_t(1) << 46) / desc->num_seqs || desc->stride_layer > (int64_t(1) << 46) / L ||
+        desc->stride_head > (int64_t(1) << 46) / H)
+        return VD_ERR_UNSUPPORTED;
     vd::AppendParams p;
     std::memset(&p, 0, sizeof p);
     const int64_t seq_off = int64_t(seq) * desc->stride_seq * es;

@@ -103,6 +103,13 @@ int main() {
                        VD_ERR_INVALID_ARG);
                 EXPECT(vd_append(&d, 0, 0, 40, rows, rows_first, rows, rows_first, i32, INT32_MAX - 39, nullptr) ==
                        VD_ERR_INVALID_ARG);
+                for (int64_t vd_cache_desc::*stride : {&vd_cache_desc::stride_seq, &vd_cache_desc::stride_layer,
+                                                       &vd_cache_desc::stride_head}) {
+                    vd_cache_desc wide = d;
+                    wide.*stride = INT64_MAX / 16 * 16;
+                    EXPECT(vd_append(&wide, 0, 0, 40, rows, rows_first, rows, rows_first, i32, 0, nullptr) ==
+                           VD_ERR_UNSUPPORTED);
+                }
                 EXPECT(vd_append(&d, S, 0, 1, rows, rows_first, rows, rows_first, i32, 0, nullptr) ==
                        VD_ERR_INVALID_ARG);
                 EXPECT(vd_select_topn(&d, f, n.data(), N.data(), u8, nullptr) == VD_ERR_HIP);
