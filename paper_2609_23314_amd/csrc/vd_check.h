@@ -32,10 +32,10 @@ inline vd_status check_desc(const vd_cache_desc *d) {
         return VD_ERR_UNSUPPORTED;
     const int64_t es = elem_bytes(d->dtype);
     // a unit's slab is addressed with 32-bit byte offsets
-    if (int64_t(d->capacity) * d->stride_slot * es > int64_t(UINT32_MAX)) return VD_ERR_UNSUPPORTED;
+    if (d->stride_slot > int64_t(UINT32_MAX) / es / d->capacity) return VD_ERR_UNSUPPORTED;
     const int64_t strides[4] = {d->stride_seq, d->stride_layer, d->stride_head, d->stride_slot};
     for (int64_t s : strides)
-        if ((s * es) % 16 != 0) return VD_ERR_INVALID_ARG;  // every row 16-byte aligned
+        if (s % (16 / es) != 0) return VD_ERR_INVALID_ARG;  // every row 16-byte aligned
     if (!aligned(d->v, 16) || (d->k && !aligned(d->k, 16))) return VD_ERR_INVALID_ARG;
     if (d->k && d->k == d->v) return VD_ERR_INVALID_ARG;
     return VD_OK;
