@@ -144,7 +144,8 @@ vd_status vd_compact(const vd_cache_desc *desc, const uint8_t *keep_mask,
  * vd_evict_step -- the whole pass (mean, score, top-N, gather) of every unit
  * in one launch: one block-processing boundary or one decode step
  * (Sec. 2.2, Eq. block_processing).  Results equal vd_score followed by
- * vd_select_topn and vd_compact.
+ * vd_select_topn and vd_compact.  Without a running sum they agree bit for bit,
+ * and in either case a unit's results do not depend on the units beside it.
  *   n_valid[s]   host; n = tokens cached after the new block was appended
  *   budget[s]    host; N >= 1; units with n <= N keep everything
  *   variant      VD_SCORE_L2 .. VD_SCORE_KEY_NORM; a key-side variant needs
@@ -297,7 +298,8 @@ size_t vd_decode_attention_noalloc_max_bytes(void);
 
 /* vd_evict_step with device scratch, through which several workgroups share the
  * rows of each unit where the cache has at most a quarter as many units as the
- * GPU has compute units.  Arguments, results and errors are vd_evict_step's, and:
+ * GPU has compute units and the longest of them holds 768 KB of scored rows or
+ * more.  Arguments, results (bit for bit) and errors are vd_evict_step's, and:
  *
  *   scratch      device, 16-byte aligned, at least vd_evict_step_split_size()
  *                bytes (may be NULL when that is 0), of any content; calls that

@@ -1,7 +1,10 @@
 // HIP kernels of the ValueDiff eviction pass for gfx950 (MI355X).
 //
 // One workgroup of 1024 threads (16 wave64s) owns one unit (sequence, layer,
-// KV head).  The pass is bound by HBM bandwidth: it streams the unit's value
+// KV head); with more units than compute units one of 512 threads may, two of
+// them to a CU, and a few long units are each scored by up to 64 workgroups
+// (step_kernel's parts).  Which of them runs changes no bit of the results.  The
+// pass is bound by HBM bandwidth: it streams the unit's value
 // rows once, with 16-byte loads per lane and a row spread over LPR lanes
 // (LPR = row bytes / 16; 16 lanes for a 128-channel bf16 row), reduces each
 // row over its lanes with DPP, and keeps everything else (scores, selection,
@@ -452,11 +455,11 @@ __device__ __forceinline__ uint32_t sum_below16(uint32_t x, int i) {
 //
 // Before the barrier that ended scoring every wave has stored its key minimum
 // in bc[w] and maximum in bc[16 + w], and hist[] and the candidate counter
-// bc[100] are zero; hist2[] (kBins entries, just past the keys) is
+// bc[100] are zero; hist2[] (THREADS entries, just past the keys) is
 // scratch.  Wave w owns the slots [j0, j1): a run of whole 64-slot blocks,
-// one more block for the first (blocks mod NW) waves, so that the four waves
-// of each SIMD (w, w+4, w+8, w+12) hold equal shares to within one block (a
-// sweep ends when the busiest SIMD has issued its waves' blocks).
+// one more block for the first (blocks mod NW) waves, so that the waves of each
+// SIMD (w, w+4, ...) hold equal shares to within one block (a sweep ends when
+// the busiest SIMD has issued its waves' blocks).
 // Histogram passes over the key range narrow it to one bin (the two histogram
 // buffers alternate, so a pass costs two barriers).  Once the bin holds at
 // most kCand keys, one sweep gathers them and publishes every wave's counts of
@@ -498,7 +501,7 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
     int need = N;       // 1-based rank of (T, J) among the keys in [lo, hi]
     int in_range = n;   // keys in [lo, hi]
     // The bin of histogram hc (bins in descending key order, wave w owning
-    // bins kBins-1-64w .. kBins-64-64w) that holds the need-th largest key:
+    // bins BINS-1-64w .. BINS-64-64w) that holds the need-th largest key:
     // its index, its count and the count of the keys above it; the other
     // buffer hn is cleared on the way (it was last read before the barrier
     // that precedes the call).
@@ -593,7 +596,7 @@ __device__ __forceinline__ int select_and_build(const uint32_t *keys, int n, int
             H.bc[48 + w] = smv;
         }
         __syncthreads();
-        // lane t holds candidate t; wave w ranks candidates w, w+16, w+32, w+48
+        // lane t holds candidate t; wave w ranks candidates w, w + NW, ...
         const int cnt = in_range;
         const bool live = lane < cnt;
         const uint32_t ck = live ? H.cand_key[lane] : 0u;
@@ -1553,8 +1556,8 @@ __global__ void __launch_bounds__(NT) compact_kernel(const UnitParams p) {
 // byte read and written once); the small blocks are bound by the launch, which
 // is why K, V and the indices share one.  A thread keeps kAppendChunks 16-byte
 // loads of K and as many of V in flight.  A workgroup takes a run of one
-// unit's rows, or, where a unit has fewer than 256 chunks (a decode step's one
-// row has 8 to 64), several units side by side.  Against torch's two copies, an
+// unit's rows, or, where a unit has at most 128 chunks of K (a decode step's one
+// row has 8 to 64), two or four units side by side.  Against torch's two copies, an
 // index fill and its copy (append and eviction pass together, us): 512 rows of
 // 256 units 77.3 -> 60.5, one row of 16 x 256 units 790 -> 686, 16 rows of one
 // unit 42.3 -> 33.6.
@@ -2022,7 +2025,7 @@ __global__ void __launch_bounds__(kAttnThreads) attn_split_kernel(const UnitPara
         return row_off(max(min(e0 + (j >> 1) * GROUPS + grp, r1 - 1), 0), ss32, cl) + z;
     };
 #pragma unroll
-    for (int j = 0; j < 2 * kAttnRows; ++j) {  // (a split past the end reads row 0, unused)
+    for (int j = 0; j < 2 * kAttnRows; ++j) {  // (a split past the end reads row n - 1, or 0, unused)
         buf[j] = load_stream((j & 1) ? vb : kb, chunk_off(r0, j, 0u));
         __builtin_amdgcn_sched_barrier(0);
     }

@@ -43,8 +43,8 @@ class EvictingCache:
         if n0 + t > self.capacity:
             raise ValueError(f"sequence {seq}: {n0} + {t} rows exceed capacity {self.capacity}")
         # one launch in place of torch's four or five (the copies, the indices, their
-        # copy): 512 rows of 256 units and their pass 77 -> 60 us, one row of one
-        # unit 42 -> 34 us, most of it launches
+        # copy): 512 rows of 256 units and their pass 77 -> 60 us, sixteen rows of
+        # one unit 42 -> 34 us, most of it launches
         if not vd.vd_append(self.k, self.v, seq, n0, k_rows, v_rows, self.pos, self.seen[seq]):
             self._append_copy(seq, k_rows, v_rows)
         self.n[seq] = n0 + t

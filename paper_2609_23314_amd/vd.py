@@ -244,7 +244,7 @@ def vd_evict_step(k, v, n_valid, budget, variant="l2", running_sum=None, pos=Non
     With ``scratch`` (a uint8 tensor of ``vd_evict_step_split_size`` bytes, not
     shared by calls that overlap, or True: the call takes its own from torch) a
     pass over few units spreads each of them over several workgroups
-    (``vd_evict_step_split`` in vd.h)."""
+    (``vd_evict_step_split`` in vd.h, which takes no ``workspace``)."""
     U, C, Dh = _units(v), v.shape[3], v.shape[4]
     desc = cache_desc(v, k, num_q_heads)
     n_h = _host_i32(n_valid, v.shape[0], "n_valid")

@@ -1,6 +1,6 @@
 """Appending rows (Sec. 2.2, Eq. block_processing): the one-launch append
 against plain copies, bit for bit, at the edges of its tiles (a workgroup
-takes 1024 16-byte chunks of one unit, or several units with fewer than 256),
+takes 1024 16-byte chunks of one unit, or several units with at most 128),
 and the rows and caches it leaves to torch's copies."""
 import ctypes
 
