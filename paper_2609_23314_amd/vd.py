@@ -224,13 +224,16 @@ def vd_evict_step_split_size(v, k=None):
 
 def _call_scratch(size, dev, stream):
     """``size`` bytes of torch's allocator for one call on its stream, which are
-    handed on in that stream's order once the call is queued (under capture they
+    handed on in that stream's order once the call is queued (under torch's capture they
     come from the graph's own pool and live as long as the graph); None where
     there is no memory for them."""
     try:
         if stream is None:
             return torch.empty(size, dtype=torch.uint8, device=dev)
-        at = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, dev)
+        at = stream
+        if not isinstance(stream, torch.cuda.Stream):  # (torch would take the handle 0 as a wish for a new stream)
+            handle = stream.cuda_stream
+            at = torch.cuda.ExternalStream(handle, dev) if handle else torch.cuda.default_stream(dev)
         with torch.cuda.stream(at):
             return torch.empty(size, dtype=torch.uint8, device=dev)
     except torch.OutOfMemoryError:

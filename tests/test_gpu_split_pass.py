@@ -200,6 +200,23 @@ class _Handle:
 
 
 @pytest.mark.parametrize("wrap", [lambda s: s, _Handle], ids=["stream", "handle"])
+@pytest.mark.parametrize("which", ["current", "side", "default"])
+def test_scratch_belongs_to_the_stream_of_its_call(which, wrap):
+    """What a call takes from torch goes back to the stream that the call ran on."""
+    s = {"current": torch.cuda.current_stream, "side": torch.cuda.Stream, "default": torch.cuda.default_stream}[which]()
+    size = 64 << 20  # a segment of its own
+    buf = vd._call_scratch(size, torch.device("cuda", torch.cuda.current_device()), wrap(s))
+    owner = [x["stream"] for x in torch.cuda.memory_snapshot()
+             if x["address"] <= buf.data_ptr() < x["address"] + x["total_size"]]
+    assert owner == [s.cuda_stream]
+    with torch.cuda.stream(s):
+        own = vd._call_scratch(size, buf.device, None)
+    owner = [x["stream"] for x in torch.cuda.memory_snapshot()
+             if x["address"] <= own.data_ptr() < x["address"] + x["total_size"]]
+    assert owner == [s.cuda_stream]
+
+
+@pytest.mark.parametrize("wrap", [lambda s: s, _Handle], ids=["stream", "handle"])
 def test_call_takes_its_own_scratch(wrap):
     k, v = [synth.random_rows((1, 2, 2, 6150, 64), torch.bfloat16, 3 + i, DEV) for i in range(2)]
     ref = [k.clone(), v.clone()]
