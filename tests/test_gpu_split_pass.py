@@ -226,3 +226,18 @@ def test_call_takes_its_own_scratch(wrap):
     vd.vd_evict_step(k, v, [6150], [6000], scratch=True, stream=wrap(s))
     torch.cuda.current_stream().wait_stream(s)
     assert torch.equal(k, ref[0]) and torch.equal(v, ref[1])
+
+
+def test_pass_without_memory_for_its_scratch(monkeypatch):
+    """Where torch has no memory for the scratch the pass runs with one workgroup per unit."""
+    k, v = [synth.random_rows((1, 2, 2, 6150, 64), torch.bfloat16, 3 + i, DEV) for i in range(2)]
+    ref = [k.clone(), v.clone()]
+    vd.vd_evict_step(*ref, [6150], [6000])
+
+    def none_left(*a, **kw):
+        raise torch.OutOfMemoryError("no memory")
+
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", none_left)
+        vd.vd_evict_step(k, v, [6150], [6000], scratch=True)
+    assert torch.equal(k, ref[0]) and torch.equal(v, ref[1])
