@@ -366,7 +366,8 @@ template <int O> __device__ __forceinline__ double pair_sum_split(double p, doub
 // apart, then 32 apart), each lane keeping half of its columns per step, in the
 // same association and operand order as summing each column over the row
 // groups: give(t, s) for each column t that this lane kept.
-template <int DT, int D, typename Give> __device__ __forceinline__ void wave_col_totals(double *acc, Give give) {
+template <int DT, int D, bool LATE = false, typename Give>
+__device__ __forceinline__ void wave_col_totals(double *acc, Give give) {
     using S = Shape<DT, D>;
     constexpr int E = S::EPL;
     if constexpr (S::LPR <= 8) {
@@ -374,7 +375,7 @@ template <int DT, int D, typename Give> __device__ __forceinline__ void wave_col
         for (int i = 0; i < E; ++i) acc[i] = xor_sum<8>(acc[i]);
     }
     int lane = lane_id();
-    asm volatile("" : "+v"(lane));  // (what follows from it is worked out here, not kept through the row stream)
+    if constexpr (LATE) asm volatile("" : "+v"(lane));  // what follows from it is worked out here, not kept
     constexpr int M16 = S::LPR <= 16 ? E / 2 : E;      // columns kept after the step over lanes 16 apart
     constexpr int M32 = S::LPR <= 32 ? M16 / 2 : M16;  // and after the one over lanes 32 apart
     static_assert(M32 >= 1, "at least one column per lane");
@@ -420,9 +421,9 @@ __device__ __forceinline__ double block_col_total(double (&acc)[PARTS][E], doubl
         if (h >= live) continue;
         if (h > 0 && !once) __syncthreads();
         int at = wave_id();
-        asm volatile("" : "+v"(at));  // (as the lane above)
+        if constexpr (PARTS > 1) asm volatile("" : "+v"(at));  // (as the lane above: the registers are needed)
         at = ((once ? h * NW : 0) + at) * D;
-        wave_col_totals<DT, D>(acc[h], [&](int t, double x) __attribute__((always_inline)) {
+        wave_col_totals<DT, D, (PARTS > 1)>(acc[h], [&](int t, double x) __attribute__((always_inline)) {
             red[lds_ix<kSiteRed>(at + t, red_cap)] = x;
         });
         if (!once) total(NW);
