@@ -221,8 +221,8 @@ vd_status launch_decode(const vd_cache_desc *desc, const float *q, float scale,
 // is too short to hide.  Measured, full against half workgroups, 1024 bf16
 // units that evict 64 rows, in no cache (us): d = 128, n = 80 37.2 and 23.4, n =
 // 320 45.7 and 29.7, n = 2176 122 and 113, n = 4160 203 and 196; d = 64, n = 1152
-// 62.2 and 40.1 (scores alone 54.8 and 41.8; of 288 units of 700 rows, which only
-// a whole LDS stages, 14.3 and 15.2, the most that is lost), n = 8492 (576
+// 62.2 and 40.1 (scores alone 54.8 and 41.8; of 700 rows, which only a whole LDS
+// stages, 288 units 14.3 and 15.2, 512 16.1 and 16.8, 1024 29.8 and 28.4), n = 8492 (576
 // units, 208 of 300 rows staged) 150 and 139; with 200 of 512 rows
 // staged (n = 2560, d = 128) 132 and 156, with 176 of 256 (eight
 // ragged sequences) 339 and 352, with 74 of 1024 (d = 256) 268 and 302.
@@ -231,12 +231,19 @@ vd_status plan_step(const vd_cache_desc *d, UnitParams &p, int ns, bool score_mo
     const int64_t units = int64_t(ns) * d->num_layers * d->num_kv_heads;
     bool argmin = !score_mode;  // every unit evicts at most one row
     for (int i = 0; i < ns; ++i) argmin = argmin && p.nN[2 * i] - 1 <= p.nN[2 * i + 1];
+    auto plan = [&](int threads, int red_waves, bool stage_all) {
+        return plan_step_lds(d, p, ns, score_mode, have_state, want_scores, threads,
+                             threads == vd::kBlock ? vd::kLdsBytes : vd::kLdsBytes / 2, red_waves, stage_all,
+                             lds_bytes) == VD_OK;
+    };
     if (units > vd::kCus && !argmin) {
-        const bool wide = d->head_dim * elem_bytes(d->dtype) > 128;
-        for (int red_waves : {vd::kWaves, vd::kHalfBlock / 64})  // room for all sums at once only if it costs nothing
-            if (plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kHalfBlock, vd::kLdsBytes / 2,
-                              red_waves, wide || red_waves == vd::kWaves, lds_bytes) == VD_OK)
-                return VD_OK;
+        for (int red_waves : {vd::kWaves, vd::kHalfBlock / 64})  // room for all sums at once only if it costs no row
+            if (plan(vd::kHalfBlock, red_waves, true)) return VD_OK;
+        if (d->head_dim * elem_bytes(d->dtype) <= 128) {
+            // (scores alone, one unit or two per CU, whose rows only a whole LDS stages)
+            if (score_mode && units <= 2 * vd::kCus && plan(vd::kBlock, vd::kWaves, true)) return VD_OK;
+            if (plan(vd::kHalfBlock, vd::kHalfBlock / 64, false)) return VD_OK;
+        }
     }
     return plan_step_lds(d, p, ns, score_mode, have_state, want_scores, vd::kBlock, vd::kLdsBytes, vd::kWaves, false,
                          lds_bytes);

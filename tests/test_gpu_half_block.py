@@ -125,3 +125,22 @@ def test_sums_do_not_depend_on_the_launch(dtype, D, variant, n):
     alone = vd.vd_score(v, [n] * S, variant)[0]
     for N2 in (N, n - 1, n):  # half workgroups, a decode step's full ones, nothing to evict
         assert torch.equal(alone, evict(0, S, N2, False)[2]), N2
+
+
+@pytest.mark.parametrize("units,n,D,threads", [(256, 80, 64, 1024), (257, 80, 64, 512), (288, 480, 64, 512),
+                                               (288, 700, 64, 1024), (512, 700, 64, 1024), (513, 700, 64, 512),
+                                               (288, 1400, 64, 512), (288, 200, 128, 512), (288, 300, 128, 1024)])
+def test_workgroup_of_the_scores(units, n, D, threads):
+    """Scores alone: half workgroups where half the LDS stages the bf16 rows, and for
+    rows of 128 bytes that it does not, unless a whole one does and there are at most
+    two units per CU."""
+    saved = (vd._lib, vd.LIB_PATH)
+    vd._lib, vd.LIB_PATH = None, lib_build.DEBUG_LIB
+    try:
+        v = synth.random_rows((1, 1, units, n, D), torch.bfloat16, n, DEV)
+        scores = vd.vd_score(v, [n])[0]
+        assert last_pass(vd.load()) == (threads, 0)
+        assert torch.equal(scores, torch.cat([vd.vd_score(v[:, :, a:a + 200], [n])[0] for a in range(0, units, 200)]))
+        assert last_pass(vd.load()) == (1024, 0)
+    finally:
+        vd._lib, vd.LIB_PATH = saved
