@@ -295,12 +295,15 @@ def _torch_follows():
                 any(type(m) is not DeviceContext for m in torch.overrides._get_current_function_mode_stack())))
 
 
-def _append_rows_ok(x, dtype, dev, L, H, D):
+def _append_strides(x, dtype, dev, L, H, D):
+    """The strides of rows that the append kernel reads, else None."""
     if not (type(x) is torch.Tensor and x.dtype == dtype and x.device == dev):
-        return False
+        return None
     shape = x.shape
-    return (len(shape) == 4 and shape[0] == L and shape[1] == H and shape[3] == D and x.stride(3) == 1
-            and not x.requires_grad and not x.is_neg())
+    if len(shape) != 4 or shape[0] != L or shape[1] != H or shape[3] != D or x.requires_grad or x.is_neg():
+        return None
+    strides = x.stride()
+    return strides if strides[3] == 1 else None
 
 
 def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
@@ -324,7 +327,8 @@ def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
         return False
     S, L, H, C, D = shape
     seq, n_old, pos0 = int(seq), int(n_old), int(pos0)
-    if not (_append_rows_ok(k_rows, dtype, dev, L, H, D) and _append_rows_ok(v_rows, dtype, dev, L, H, D)):
+    ks, vs = _append_strides(k_rows, dtype, dev, L, H, D), _append_strides(v_rows, dtype, dev, L, H, D)
+    if ks is None or vs is None:
         return False
     t = k_rows.shape[2]
     if not (v_rows.shape[2] == t and t > 0 and 0 <= seq < S and 0 <= n_old <= C and 0 <= pos0 < 2 ** 31):
@@ -332,12 +336,13 @@ def vd_append(k, v, seq, n_old, k_rows, v_rows, pos=None, pos0=0):
     if pos is not None and not (type(pos) is torch.Tensor and pos.dtype == torch.int32 and pos.device == dev
                                 and pos.shape == (S * L * H, C) and pos.is_contiguous()):
         return False
-    if dev.index != torch.cuda.current_device():
+    if dev.index != torch._C._cuda_getDevice():
         return False
-    ks, vs = _Strides3(*k_rows.stride()[:3]), _Strides3(*v_rows.stride()[:3])
-    desc = VdCacheDesc(k.data_ptr(), v.data_ptr(), _dtype_code(v), S, L, H, H, D, C, *strides[:4])
-    st = load().vd_append(ctypes.byref(desc), seq, n_old, t, k_rows.data_ptr(), ks,
-                          v_rows.data_ptr(), vs, _ptr(pos), pos0, _stream(dev, None))
+    desc = VdCacheDesc(k.data_ptr(), v.data_ptr(), VD_DTYPE_BF16 if dtype == torch.bfloat16 else VD_DTYPE_F32,
+                       S, L, H, H, D, C, *strides[:4])
+    st = load().vd_append(ctypes.byref(desc), seq, n_old, t, k_rows.data_ptr(), _Strides3(*ks[:3]),
+                          v_rows.data_ptr(), _Strides3(*vs[:3]), None if pos is None else pos.data_ptr(), pos0,
+                          torch._C._cuda_getCurrentRawStream(dev.index))
     if st in (VD_ERR_INVALID_ARG, VD_ERR_UNSUPPORTED):
         return False
     _check("vd_append", st)
